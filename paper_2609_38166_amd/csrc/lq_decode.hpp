@@ -119,53 +119,6 @@ __device__ __forceinline__ double h2d(uint32_t w, int hi) {
     return (double)h2f((uint16_t)(w >> (16 * hi)));
 }
 
-// Cross-row swaps of a double (two 32-bit halves).
-__device__ __forceinline__ void swap32_d(double a, double b, double &ra, double &rb) {
-    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
-    ra = __hiloint2double(hi[0], lo[0]);
-    rb = __hiloint2double(hi[1], lo[1]);
-}
-__device__ __forceinline__ void swap16_d(double a, double b, double &ra, double &rb) {
-    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
-    ra = __hiloint2double(hi[0], lo[0]);
-    rb = __hiloint2double(hi[1], lo[1]);
-}
-
-// Sum of x over the 4 slots (16-lane rows) of a wave, for 8 values per lane,
-// as a reduce-scatter: lane (row rho, l16) returns the sums of values 2 rho
-// and 2 rho + 1.  A cross-row swap of registers (a, b) hands the lower rows
-// the upper rows' a and the upper rows the lower rows' b, so own + received is
-// the sum wanted in every lane without a select.
-__device__ __forceinline__ void rows4_reduce_scatter(const float *x, float &s0, float &s1) {
-    float h[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {           // rows rho, rho ^ 2: keep values 4 (rho >> 1) + 0..3
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[i]), __float_as_uint(x[4 + i]), false, false);
-        h[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    // rows rho, rho ^ 1: keep 2 of those 4
-    const auto r0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(h[0]), __float_as_uint(h[2]), false, false);
-    const auto r1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(h[1]), __float_as_uint(h[3]), false, false);
-    s0 = __uint_as_float(r0[0]) + __uint_as_float(r0[1]);
-    s1 = __uint_as_float(r1[0]) + __uint_as_float(r1[1]);
-}
-__device__ __forceinline__ void rows4_reduce_scatter(const double *x, double &s0, double &s1) {
-    double h[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        double a, b;
-        swap32_d(x[i], x[4 + i], a, b);
-        h[i] = a + b;
-    }
-    double a, b;
-    swap16_d(h[0], h[2], a, b);
-    s0 = a + b;
-    swap16_d(h[1], h[3], a, b);
-    s1 = a + b;
-}
-
 // Largest value of x over the 64 lanes of the wave (every lane gets it).
 __device__ __forceinline__ int wave_max_i32(int x) {
     x = max(x, __builtin_amdgcn_update_dpp(0, x, DPP_XOR1, 0xF, 0xF, false));

@@ -81,6 +81,82 @@ __device__ __forceinline__ float wave_sum(float x) {
     return x;
 }
 
+// Cross-row swaps of a double (two 32-bit halves).
+__device__ __forceinline__ void swap32_d(double a, double b, double &ra, double &rb) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    ra = __hiloint2double(hi[0], lo[0]);
+    rb = __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ void swap16_d(double a, double b, double &ra, double &rb) {
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    ra = __hiloint2double(hi[0], lo[0]);
+    rb = __hiloint2double(hi[1], lo[1]);
+}
+
+// Sum of x over the 4 slots (16-lane rows) of a wave, for 8 values per lane,
+// as a reduce-scatter: lane (row rho, l16) returns the sums of values 2 rho
+// and 2 rho + 1.  A cross-row swap of registers (a, b) hands the lower rows
+// the upper rows' a and the upper rows the lower rows' b, so own + received is
+// the sum wanted in every lane without a select.
+__device__ __forceinline__ void rows4_reduce_scatter(const float *x, float &s0, float &s1) {
+    float h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {           // rows rho, rho ^ 2: keep values 4 (rho >> 1) + 0..3
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[i]), __float_as_uint(x[4 + i]), false, false);
+        h[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    // rows rho, rho ^ 1: keep 2 of those 4
+    const auto r0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(h[0]), __float_as_uint(h[2]), false, false);
+    const auto r1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(h[1]), __float_as_uint(h[3]), false, false);
+    s0 = __uint_as_float(r0[0]) + __uint_as_float(r0[1]);
+    s1 = __uint_as_float(r1[0]) + __uint_as_float(r1[1]);
+}
+__device__ __forceinline__ void rows4_reduce_scatter(const double *x, double &s0, double &s1) {
+    double h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        double a, b;
+        swap32_d(x[i], x[4 + i], a, b);
+        h[i] = a + b;
+    }
+    double a, b;
+    swap16_d(h[0], h[2], a, b);
+    s0 = a + b;
+    swap16_d(h[1], h[3], a, b);
+    s1 = a + b;
+}
+
+// The same reduce-scatter with the largest value instead of the sum.
+__device__ __forceinline__ void rows4_max_scatter(const float *x, float &s0, float &s1) {
+    float h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[i]), __float_as_uint(x[4 + i]), false, false);
+        h[i] = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    }
+    const auto r0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(h[0]), __float_as_uint(h[2]), false, false);
+    const auto r1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(h[1]), __float_as_uint(h[3]), false, false);
+    s0 = fmaxf(__uint_as_float(r0[0]), __uint_as_float(r0[1]));
+    s1 = fmaxf(__uint_as_float(r1[0]), __uint_as_float(r1[1]));
+}
+
+// 64-bit DPP move: lane n of each 16-lane row to every lane of the row.  (The
+// intrinsic is declared by name: the builtin takes 32-bit values only, and the
+// two 32-bit moves it would need cost twice as much.)
+extern "C" __device__ long long lq_update_dpp_i64(long long old, long long src, int ctrl, int row_mask, int bank_mask,
+                                                  bool bound_ctrl) __asm("llvm.amdgcn.update.dpp.i64");
+template <int LANE>
+__device__ __forceinline__ double row_bcast(double x) {
+    const long long b = __builtin_bit_cast(long long, x);
+    return __builtin_bit_cast(double, lq_update_dpp_i64(b, b, 0x150 + LANE, 0xF, 0xF, true));
+}
+template <int LANE>
+__device__ __forceinline__ float row_bcast(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x150 + LANE, 0xF, 0xF, true));
+}
+
 // ---- fp16 / bf16 / fp8 conversions ---------------------------------------------
 __device__ __forceinline__ float h2f(uint16_t h) {
     return (float)__builtin_bit_cast(_Float16, h);

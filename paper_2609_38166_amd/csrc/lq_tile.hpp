@@ -3,14 +3,33 @@
 // Whole-tile kernels: quantize a given state, commit a window, dequantize.
 //
 // One 256-thread workgroup (4 waves) owns one 128 x 128 tile held in
-// registers: thread (kb, vb) keeps the 8 x 8 block M[8kb .. 8kb+7][8vb .. 8vb+7]
-// of the state in paper orientation (row = key channel).  kb is the lane's
-// column inside its 16-lane DPP row, so sums over key channels stay inside a
-// wave; sums over value channels go through LDS.  Three workgroups share a CU
-// (168 VGPRs per lane, 50 KiB of LDS each): the 128 registers of the fp64
-// block leave 40 for everything else, so the code below keeps few values
-// live across phases (lane coordinates re-derived where used, records kept
-// packed, the next pass's records copied straight into LDS).
+// registers: wave w owns key channels 32 w .. 32 w + 31, and lane (row j, i) of
+// it the 8 x 8 block M[32 w + 8 j + a][8 i + b] of the state in paper
+// orientation (row = key channel).  A sum over value channels stays inside a
+// 16-lane row; a sum over key channels crosses the wave's rows in registers and
+// the waves through LDS: one barrier per power sweep.  A vector over key
+// channels never leaves its wave.  Three workgroups share a CU (166 VGPRs per
+// lane, 47 KiB of LDS each): the 128 registers of the fp64 block leave 40 for
+// everything else, so the code below keeps few values live across phases (lane
+// coordinates re-derived where used, the next pass's records copied straight
+// into LDS).
+//
+// What bounds it: fp64 issue, and in the sweeps the LDS transposes and the
+// barrier beside it.  A sweep is 128 FMA per lane (0.27 us per tile and CU at the
+// 2.05 GHz that the card holds under them); it takes 0.40 us with three
+// workgroups per CU and 0.73 us with one.  Measured at r = 8, 4 sweeps against
+// the layout before (a thread's block in a row of key blocks, two barriers and
+// five LDS round trips a sweep): quantize 48.7 -> 39.7 us for 32 tiles, 1578 ->
+// 1455 us for 16384; commit of 64 records (per-channel gate) 75.6 -> 57.3 us
+// for 32 tiles, 182 -> 160 us for 1024, 1245 -> 1110 us for 8192.
+//
+// The rank-one terms of the reconstruction (records, Compensator Tokens) go
+// through the fp64 matrix cores, v_mfma_f64_16x16x4: the same rate per cycle as
+// the vector unit's FMA, but one instruction per 16, two LDS reads per 16 x 16
+// product instead of four per 64 FMA, and less power: 77 TFLOP/s at 2.38 GHz
+// against 67 at 2.2 in a loop of nothing else.  Its accumulators are the 8 x 8
+// blocks (the operand rows are permuted to make them so).  Reconstruction and
+// fp32 store of 8192 tiles with 64 records and 8 tokens: 490 -> 425 us.
 //
 //   commit   : reconstruct S_p = Gamma_{1:p}[C dequant(Z) + K~ U~^T]
 //              + sum_j Gamma_{j+1:p} k~_j u_j^T  (Sec. 3.4 Eq. (smooth)),
@@ -42,17 +61,10 @@ namespace lq {
 
 namespace {
 
-constexpr int TCH = 16;     // rank-one records staged per pass
+constexpr int TCH = 8;      // records staged per pass
 constexpr int TT = 256;     // threads per tile
-constexpr int NVB = 16;     // value blocks
+constexpr int NW = TT / 64; // waves: each owns 32 key channels
 constexpr int VPT = 8;      // value channels per thread
-
-// Per-key-channel vectors in LDS are stored swizzled: channel 8kb+a sits at
-// position 16a+kb, so the 16 lanes of a DPP row (kb = 0..15) touch 16
-// consecutive 8-byte words and never share a bank.  A thread t < 128 that
-// works on "position t" works on channel KCH(t).
-__device__ __forceinline__ constexpr int KP(int kb, int a) { return 16 * a + kb; }
-__device__ __forceinline__ constexpr int KCH(int t) { return 8 * (t & 15) + (t >> 4); }
 
 // The 8 codes of row v (value channel), key channels 8kb..8kb+7: 8 bytes for
 // the byte formats, 4 for INT4, 6 (three 16-bit words) for INT6, 16 (eight
@@ -106,6 +118,8 @@ __device__ __forceinline__ void store_codes8(uint8_t *codes, int tile, int v, in
     }
 }
 
+typedef double v4d __attribute__((ext_vector_type(4)));
+
 struct TileArgs {
     uint8_t *codes;
     float *scale;
@@ -127,88 +141,119 @@ struct TileArgs {
     int smooth_on;
 };
 
+// Codes that the reconstruction copies into LDS when it starts; the BF16 state
+// (32 KiB a tile) is loaded where it is used.
+template <int CODE> struct CodesInLds { static constexpr bool value = !IsBF16<CODE>::value; };
+
 struct TileShared {
     union {
-        double part[NVB][D];    // per-value-block partials of a sum over value channels
-        double pre[TCH][D];     // record staging: decay of every newer record
-    };
-    double vec[D];          // broadcast vector
-    double nrm[2];          // per-wave partial squared norms
-    union {
-        struct {            // reconstruction phase
-            double key[TCH][D];     // staged record keys, decay folded in
-            float val[TCH][D];      // staged record values
-            float bp[TCH][D];       // decay of each staged record
-            double tot[D];          // decay of a whole pass
+        struct {                            // reconstruction
+            double key[NW][TCH][32];        // a wave's record keys, decay folded in
+            double val[2][TCH][D];          // record values, two passes in turn (channel 8 i + b at 16 b + i)
+            uint4 raw_ka[NW][64];           // copied records: a wave's keys, then decays
+            uint4 raw_u[NW][32];            // two records' values of each wave
+            uint4 codes[D * D / 16];        // rows rotated by (v >> 3)
+            float scale[D];
+            float smooth[D];
         };
-        double rowp[NVB][8 * 17];   // fit phase: per-row partials of sums over key blocks
+        struct {                            // fit
+            double part[2][NW][D];          // per-wave partials of a sum over key channels, two in turn
+            double nrm[2][NW];              // per-wave partial squared norms
+            double vec[NW][D];              // a wave's copy of a summed vector (VP order)
+            double red[TT / 16][8 * 17];    // row-private transposes of a sum over value channels
+        };
     };
 };
 
-// Sums over value channels in two halves: each thread stores its value
-// block's partial for channel 8kb+a as soon as it has it (put_part), then
-// sum_parts adds the 16 value blocks; thread t < 128 gets channel KCH(t).
-__device__ __forceinline__ void put_part(TileShared &sh, int a, double p, int kb, int vb) {
-    sh.part[vb][KP(kb, a)] = p;
-}
-__device__ __forceinline__ double sum_parts(TileShared &sh) {
+// Order of a value vector in LDS: channel v = 8 i + 2 q + e at 32 q + 2 i + e, so
+// the 16 lanes of a row that read pair q of their block touch 256 consecutive
+// bytes, and lane (row j, i) of a wave that holds pair j sits at 2 * lane.
+
+// Sum over key channels of v[b] (b = 0..7: this thread's value channels, its 8
+// key channels added up): over the wave's 4 rows by cross-row swaps, over the
+// 4 waves through LDS.  One barrier; `buf` alternates between calls, so a
+// call's writes meet only reads that the previous call's barrier has ended.
+// Lane (row j, i) receives channels 8 i + 2 j and 8 i + 2 j + 1.
+__device__ __forceinline__ double2 sum_keys(TileShared &sh, const double *v, int buf, int tid) {
+    const int lane = tid & 63, w = tid >> 6;
+    double s0, s1;
+    rows4_reduce_scatter(v, s0, s1);
+    *(double2 *)&sh.part[buf][w][2 * lane] = make_double2(s0, s1);
     __syncthreads();
-    double s = 0.0;
-    const int t = threadIdx.x;
-    if (t < D) {
-        double v[4] = {sh.part[0][t], sh.part[1][t], sh.part[2][t], sh.part[3][t]};
+    double2 p[NW];
 #pragma unroll
-        for (int j = 4; j < NVB; ++j) v[j & 3] += sh.part[j][t];
-        s = (v[0] + v[1]) + (v[2] + v[3]);
-    }
-    return s;
+    for (int x = 0; x < NW; ++x) p[x] = *(const double2 *)&sh.part[buf][x][2 * lane];
+    return make_double2((p[0].x + p[1].x) + (p[2].x + p[3].x), (p[0].y + p[1].y) + (p[2].y + p[3].y));
 }
 
-// Threads t < 128 publish x (channel KCH(t)) to sh.vec, which every thread
-// then reads where it needs it (channel 8kb+a at KP(kb, a)); with_norm also
-// returns the squared norm of the whole vector.  The barrier also ends every
-// read of sh.part issued before the call.
-__device__ __forceinline__ double publish(TileShared &sh, double x, bool with_norm) {
-    const int t = threadIdx.x;
-    if (t < D) {
-        sh.vec[t] = x;
-        if (with_norm) {
-            const double s = wave_sum(x * x);
-            if ((t & 63) == 0) sh.nrm[t >> 6] = s;
-        }
+// The lane's pair of a value vector to every lane of the wave: v[b] = channel
+// 8 i + b (through the wave's own LDS copy; no barrier).
+__device__ __forceinline__ void share_pairs(TileShared &sh, double2 t, double *v, int tid) {
+    const int lane = tid & 63, w = tid >> 6, i = lane & 15;
+    __builtin_amdgcn_wave_barrier();
+    *(double2 *)&sh.vec[w][2 * lane] = t;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double2 y = *(const double2 *)&sh.vec[w][32 * q + 2 * i];
+        v[2 * q] = y.x;
+        v[2 * q + 1] = y.y;
     }
-    __syncthreads();
-    if (!with_norm) return 0.0;
-    int z = 0;                           // a zero made where it is used (not held across the fit)
-    asm volatile("v_mov_b32 %0, 0" : "=v"(z));
-    return sh.nrm[z] + sh.nrm[z + 1];
+    __builtin_amdgcn_wave_barrier();
 }
 
-// Sum v[b] (b = 0..7, this thread's value channels) over the 16 key blocks
-// of its DPP row and return the 8 sums, times `scale`, in v.  The row's 16
-// lanes belong to one wave, so a row-private LDS region needs no workgroup
-// barrier: lane kb stores its partials at [b][kb] (rows of 17 words, so the
-// words a read touches sit in distinct banks, and consecutive rows start 16
-// banks apart); lane kb then sums channel kb & 7 over key blocks 8h .. 8h + 7
-// (h = kb >> 3), adds lane kb ^ 8's half by a row rotation, and lanes kb < 8
-// park the sums in the row's spare words, which every lane reads back.
-__device__ __forceinline__ void row_sum8(TileShared &sh, double *v, int kb, int vb, double scale) {
-    double *r = sh.rowp[vb];
-#pragma unroll
-    for (int b = 0; b < 8; ++b) r[17 * b + kb] = v[b];
-    __builtin_amdgcn_wave_barrier();
-    const int c = kb & 7, o = 17 * c + 8 * (kb >> 3);
-    double t[4] = {r[o], r[o + 1], r[o + 2], r[o + 3]};
-#pragma unroll
-    for (int l = 4; l < 8; ++l) t[l & 3] += r[o + l];
-    double h = (t[0] + t[1]) + (t[2] + t[3]);
-    h += dpp<DPP_ROR8>(h);
-    if (kb < 8) r[17 * c + 16] = h * scale;
+// Sum over value channels of p[a] (a = 0..7: this thread's key channels, its 8
+// value channels added up) over the 16 lanes of its row, which lie in one
+// wave: a row-private LDS transpose, no barrier.  Lane i receives key channel
+// i & 7.  Channels are 17 words apart: neither the writes (16 lanes of one
+// channel) nor the reads (lane (c, h): 8 lanes of channel c) share a bank.
+__device__ __forceinline__ double sum_values(TileShared &sh, const double *p, int tid) {
+    const int i = tid & 15, c = i & 7, h = i >> 3;
+    double *r = sh.red[tid >> 4];
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int b = 0; b < 8; ++b) v[b] = r[17 * b + 16];
+    for (int a = 0; a < 8; ++a) r[17 * a + i] = p[a];
     __builtin_amdgcn_wave_barrier();
+    double s[8];
+#pragma unroll
+    for (int l = 0; l < 8; ++l) s[l] = r[17 * c + 8 * h + l];
+    __builtin_amdgcn_wave_barrier();
+    const double z = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+    return z + dpp<DPP_ROR8>(z);
 }
+
+// The value of lane a (0..7, a constant once unrolled) of the row: key channel a
+// of the thread's block.
+template <typename T>
+__device__ __forceinline__ T row_lane(T z, int a) {
+    switch (a) {
+        case 0: return row_bcast<0>(z);
+        case 1: return row_bcast<1>(z);
+        case 2: return row_bcast<2>(z);
+        case 3: return row_bcast<3>(z);
+        case 4: return row_bcast<4>(z);
+        case 5: return row_bcast<5>(z);
+        case 6: return row_bcast<6>(z);
+        default: return row_bcast<7>(z);
+    }
+}
+
+// Sum over the wave of z, which lanes i and i + 8 of a row both hold.
+__device__ __forceinline__ double wave_sum_half(double z) {
+    z = row16_sum(z);
+    double a, b;
+    swap32_d(z, z, a, b);
+    z = a + b;
+    swap16_d(z, z, a, b);
+    return 0.5 * (a + b);
+}
+
+__device__ __forceinline__ double sum_nrm(const TileShared &sh, int buf) {
+    return (sh.nrm[buf][0] + sh.nrm[buf][1]) + (sh.nrm[buf][2] + sh.nrm[buf][3]);
+}
+
+template <int N>
+__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 
 // The whole-tile work of one workgroup.  p_given >= 0 (window commit only)
 // is the number of buffered records, taken instead of the tile's rec_len and
@@ -216,54 +261,43 @@ __device__ __forceinline__ void row_sum8(TileShared &sh, double *v, int kb, int 
 // count it has just made.
 template <int GATE, int CODE, int MODE>
 __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int tile, int p_given) {
-    const int tid = threadIdx.x;
-    int kb = tid & 15;                              // key block of 8 channels (DPP column)
-    int vb = tid >> 4;                              // value block of VPT channels (0..15)
-    // re-derive the lane coordinates from an opaque thread index, so that the
-    // compiler recomputes the addresses built from them instead of holding
-    // them in registers across phases
+    // lane coordinates: value block i, row j of the wave, wave w; re-derived from
+    // an opaque thread index at phase boundaries, so that the compiler recomputes
+    // the addresses built from them instead of holding them across phases
+    int tid = threadIdx.x, i = tid & 15, j = (tid >> 4) & 3, kb = tid >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     auto refresh = [&]() {
         int t = (int)threadIdx.x;
         asm volatile("" : "+v"(t));
-        kb = t & 15;
-        vb = t >> 4;
+        tid = t;
+        i = t & 15;
+        j = (t >> 4) & 3;
+        kb = t >> 4;                                // key block of 8 channels (4 w + j)
     };
     const size_t tvec = (size_t)tile * D;
     const int r = A.n_comp;
 
-    double m[8][VPT];                               // m[a][b] = M[8kb+a][VPT*vb+b]
+    // the block: M(a, b) = M[8 kb + a][8 i + b], in the accumulator layout of
+    // v_mfma_f64_16x16x4 (accumulator (a >> 2, b): row j + 4 (a & 3), column i)
+    v4d m4[2][VPT];
+#define M(a, b) m4[(a) >> 2][b][(a) & 3]
+    // holds the block in registers at a phase boundary
+    auto pin = [&]() {
+#pragma unroll
+        for (int b = 0; b < VPT; ++b) asm volatile("" : "+v"(m4[0][b]), "+v"(m4[1][b]));
+    };
 
     if (MODE == TILE_QUANTIZE) {
         const float *S = A.S_in + (size_t)tile * D * D;
 #pragma unroll
         for (int b = 0; b < VPT; ++b) {
-            const float4 *row = (const float4 *)(S + (size_t)(VPT * vb + b) * D + 8 * kb);
+            const float4 *row = (const float4 *)(S + (size_t)(VPT * i + b) * D + 8 * kb);
             const float4 lo = row[0], hi = row[1];
-            m[0][b] = lo.x; m[1][b] = lo.y; m[2][b] = lo.z; m[3][b] = lo.w;
-            m[4][b] = hi.x; m[5][b] = hi.y; m[6][b] = hi.z; m[7][b] = hi.w;
+            M(0, b) = lo.x; M(1, b) = lo.y; M(2, b) = lo.z; M(3, b) = lo.w;
+            M(4, b) = hi.x; M(5, b) = hi.y; M(6, b) = hi.z; M(7, b) = hi.w;
         }
     } else {
-        // Every global load of the reconstruction is issued here, ahead of
-        // its first use: rec_len, the codes and scales of this thread's
-        // block, the compensators (one 16-byte segment per thread) and the
-        // first pass of records.
         const int p = p_given >= 0 ? p_given : A.rec_len[tile];
-        const int l16 = tid & 15, ts = tid >> 4;    // staging: segment, slot
-        typename Codes8<CODE>::type zp[VPT];
-#pragma unroll
-        for (int b = 0; b < VPT; ++b) zp[b] = load_codes8<CODE>(A.codes, tile, VPT * vb + b, kb);
-        // (the BF16 state has unit scales and no smoothing; its arrays are not read)
-        const float4 one4 = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
-        const bool bf = IsBF16<CODE>::value;
-        const float4 dl0 = bf ? one4 : *(const float4 *)(A.scale + tvec + VPT * vb);
-        const float4 dl1 = bf ? one4 : *(const float4 *)(A.scale + tvec + VPT * vb + 4);
-        const float4 c0 = bf ? one4 : *(const float4 *)(A.smooth + tvec + 8 * kb);
-        const float4 c1 = bf ? one4 : *(const float4 *)(A.smooth + tvec + 8 * kb + 4);
-        uint4 ck = make_uint4(0, 0, 0, 0), cu = ck;
-        if (ts < r) {
-            ck = *(const uint4 *)(A.comp_k + ((size_t)tile * r + ts) * D + 8 * l16);
-            cu = *(const uint4 *)(A.comp_u + ((size_t)tile * r + ts) * D + 8 * l16);
-        }
         if (p < 0 || p > A.window) {                                  // corrupt: tile untouched
             if (tid == 0) atomicOr(A.err, (int)LQ_DEVERR_BAD_REC_LEN);
             return;
@@ -272,290 +306,311 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
             const int req = tile / A.heads_v;
             if (p == 0 || (p_given < 0 && A.mask && A.mask[req] == 0)) return;   // uniform: tile untouched
         }
-        // records in passes of TCH, oldest pass first; slot ts of a pass takes
-        // record lo+ts, lane l16 its 8-channel / 8-value segment.
-        const size_t rbase = (size_t)tile * A.window;
-        // the tile's record arrays as uniform bases, the lane's part as a 32-bit
-        // offset (no per-lane 64-bit address is held across the passes)
-        const uint16_t *rkb = A.rec_k + rbase * D, *rub = A.rec_u + rbase * D;
-        const uint16_t *rab = A.rec_a + rbase * (GATE ? D : 1);
-        // A pass's records are copied straight into LDS (the raw FP16 words,
-        // in the record-staging area, which is idle while the previous pass's
-        // records are applied), so no register holds them across a pass;
-        // wave w copies records lo + 4w .. lo + 4w + 3.  The scalar gate's one
-        // decay per record is loaded into a register.
-        uint4 (*raw)[TCH][16] = (uint4 (*)[TCH][16])sh.pre;   // [key, corr, decay][record][segment]
-        uint32_t ras = 0;
-        auto load_pass = [&](int lo_, int hi_) {
-            const int t = (int)threadIdx.x;
-            const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-            const int rr = lo_ + 4 * w + ((t & 63) >> 4);
-            const uint32_t off = (uint32_t)rr * D + 8u * (t & 15);
-            if (rr < hi_) {
-                dma16(rkb + off, lds_addr(&raw[0][4 * w][0]));
-                dma16(rub + off, lds_addr(&raw[1][4 * w][0]));
-                if (GATE) dma16(rab + off, lds_addr(&raw[2][4 * w][0]));
-            }
-            if (!GATE) {
-                const int rs = lo_ + (t >> 4);
-                if (rs < hi_) ras = rab[rs];
+        // The rank-one terms in passes of TCH: the records newest first (the
+        // decay of everything newer than a pass is carried along), then the
+        // Compensator Tokens, which decay like the base.  A pass's operands are
+        // copied straight into LDS during the pass before: a wave copies its 32
+        // key channels of all records, and all value channels of two records.
+        const int nrp = (p + TCH - 1) / TCH, passes = nrp + (r + TCH - 1) / TCH;
+        const size_t rbase = (size_t)tile * A.window * D, cbase = (size_t)tile * r * D;
+        const uint16_t *rab = A.rec_a + (size_t)tile * A.window * (GATE ? D : 1);
+        // (pinned in scalar registers: the compiler would select between the kernel's
+        // arguments through memory)
+        const uint16_t *rkb = A.rec_k + rbase, *rub = A.rec_u + rbase, *ckb = A.comp_k + cbase, *cub = A.comp_u + cbase;
+        asm volatile("" : "+s"(rkb), "+s"(rub), "+s"(rab), "+s"(ckb), "+s"(cub));
+        uint32_t ras = 0;                           // scalar gate: the decay of slot lane & 7
+        auto bounds = [&](int t, int &lo, int &n) {
+            if (t < nrp) {
+                const int hi = p - TCH * t;
+                lo = hi > TCH ? hi - TCH : 0;
+                n = hi - lo;
+            } else {
+                lo = TCH * (t - nrp);
+                n = r - lo < TCH ? r - lo : TCH;
             }
         };
-        if (p > 0) load_pass(0, p < TCH ? p : TCH);
+        auto load_pass = [&](int t) {
+            int lo, n;
+            bounds(t, lo, n);
+            const bool rec = t < nrp;
+            const uint16_t *pk = rec ? rkb : ckb, *pu = rec ? rub : cub;
+            const int l = (int)threadIdx.x & 63, c = l & 31, s = c >> 2;
+            const uint32_t off = (uint32_t)(lo + s) * D + 32 * w + 8 * (c & 3);
+            if (s < n && (l < 32 || (GATE && rec)))
+                dma16((l < 32 ? pk : rab) + off, lds_addr(&sh.raw_ka[w][0]));
+            const int su = 2 * w + (c >> 4);
+            if (l < 32 && su < n) dma16(pu + (uint32_t)(lo + su) * D + 8 * (c & 15), lds_addr(&sh.raw_u[w][0]));
+            if (!GATE) {
+                // (out of the asm above the pointer is generic: cast back to global)
+                using gh = const __attribute__((address_space(1))) uint16_t;
+                ras = rec && (l & 7) < n ? (uint32_t)((gh *)rab)[lo + (l & 7)] : 0x3C00u;
+            }
+        };
+        if (passes > 0) load_pass(0);
+        // the base's codes, row v's 16-byte chunk c at chunk (c + (v >> 3)) mod SEGS of
+        // its row: the 16 rows that a read touches then spread over the banks
+        constexpr int SEGS = D * CodeFmt<CODE>::BITS / 8 / 16, NCP = CodesInLds<CODE>::value ? D * SEGS / TT : 0;
+        if constexpr (!IsBF16<CODE>::value) {
+            if (tid < 32) dma16(A.scale + tvec + 4 * tid, lds_addr(sh.scale));
+            if (w == 1 && (tid & 63) < 32) dma16(A.smooth + tvec + 4 * (tid & 63), lds_addr(sh.smooth));
+        }
+        if constexpr (CodesInLds<CODE>::value) {
+            const uint4 *zt = (const uint4 *)(A.codes + (size_t)tile * D * SEGS * 16);
+#pragma unroll
+            for (int x = 0; x < NCP; ++x) {
+                const int P = TT * x + tid, v = P / SEGS, c = P % SEGS;
+                dma16(zt + v * SEGS + (c + 16 * SEGS - (v >> 3)) % SEGS, lds_addr(&sh.codes[TT * x + 64 * w]));
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < 8; ++a)
+#pragma unroll
+            for (int b = 0; b < VPT; ++b) M(a, b) = 0.0;
 
-        // window-start base C dequant(Z) (Sec. 3.4 Eq. (smooth))
+        // decay of everything newer than the pass: key channel 32 w + (lane & 31)
+        double carry = 1.0;
+#pragma unroll 1
+        for (int t = 0; t < passes; ++t) {
+            refresh();
+            int lo, n;
+            bounds(t, lo, n);
+            const bool rec = t < nrp;
+            if (t == 0) wait_vm<NCP>();             // the first pass has landed (the codes may follow)
+            else wait_vm_all();
+            {
+                // keys: lane (c, h) folds the decay into slots 7 - 4 h - e, e = 0..3, newest first
+                const int c = tid & 31, h = (tid >> 5) & 1;
+                const uint16_t *raw = (const uint16_t *)sh.raw_ka[w];
+                double P, av[4];
+                const int s0 = 7 - 4 * h;
+                uint32_t rk[4], ra[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    rk[e] = raw[32 * (s0 - e) + c];
+                    if (GATE) ra[e] = raw[TCH * 32 + 32 * (s0 - e) + c];
+                }
+                const uint2 u = ((const uint2 *)sh.raw_u[w])[tid & 63];
+                if (GATE) {
+                    // (all reads issued together; a slot past the pass's records, and every
+                    // token, has decay 1)
+                    asm volatile("" : "+v"(ra[0]), "+v"(ra[1]), "+v"(ra[2]), "+v"(ra[3]));
+                    const int last = rec ? n : 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) av[e] = (double)h2f((uint16_t)(s0 - e < last ? ra[e] : 0x3C00u));
+                    const double q = (av[0] * av[1]) * (av[2] * av[3]);
+                    double q0, q1;
+                    swap32_d(q, q, q0, q1);         // the newer and the older half's product
+                    P = h ? carry * q0 : carry;
+                    carry *= q0 * q1;
+                } else {
+                    float f[8];
+#pragma unroll
+                    for (int s = 0; s < 8; ++s) f[s] = row_lane(h2f((uint16_t)ras), s);
+                    double Ps[9];
+                    Ps[8] = carry;
+#pragma unroll
+                    for (int s = 7; s >= 0; --s) Ps[s] = Ps[s + 1] * (double)f[s];
+                    carry = Ps[0];
+                    P = h ? Ps[4] : Ps[8];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) av[e] = (double)(h ? f[3 - e] : f[7 - e]);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    sh.key[w][s0 - e][c] = P * (double)h2f((uint16_t)(s0 - e < n ? rk[e] : 0u));
+                    P *= av[e];
+                }
+                // values: lane (record, 4-channel segment) of the wave's two records,
+                // channel 8 i + b at 16 b + i
+                const int s = 2 * w + h;
+                double *val = &sh.val[t & 1][s][64 * (c & 1) + (c >> 1)];
+                const uint32_t u0 = s < n ? u.x : 0u, u1 = s < n ? u.y : 0u;
+                val[0] = (double)h2f((uint16_t)u0);
+                val[16] = (double)h2f((uint16_t)(u0 >> 16));
+                val[32] = (double)h2f((uint16_t)u1);
+                val[48] = (double)h2f((uint16_t)(u1 >> 16));
+            }
+            __syncthreads();
+            // this wave's raw copies have been read: the next pass may land there
+            if (t + 1 < passes) load_pass(t + 1);
+            refresh();
+            // four slots per matrix product: lane (j, i) brings slot 4 g + j of key row
+            // i (channel 8 (i & 3) + 4 x + (i >> 2), so that the accumulators hold this
+            // thread's block) and of value column i
+            const double *krow = &sh.key[w][j][8 * (i & 3) + (i >> 2)];
+            const double *vrow = &sh.val[t & 1][j][i];
+#pragma unroll 1
+            for (int g = 0; g < n; g += 4) {
+                const double k0 = krow[32 * g], k1 = krow[32 * g + 4];
+#pragma unroll
+                for (int b = 0; b < VPT; ++b) {
+                    const double u = vrow[D * g + 16 * b];
+                    m4[0][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(k0, u, m4[0][b], 0, 0, 0);
+                    m4[1][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(k1, u, m4[1][b], 0, 0, 0);
+                }
+            }
+        }
+        wait_vm_all();
+        refresh();
+        sh.key[w][0][tid & 31] = carry;             // Gamma_{1:p} (both half-waves hold it)
+        __syncthreads();
+        // + the window-start base Gamma_{1:p} C dequant(Z) (Sec. 3.4 Eq. (smooth); the
+        // BF16 state has unit scales and no smoothing, its arrays are not read)
         {
-            const float dv[8] = {dl0.x, dl0.y, dl0.z, dl0.w, dl1.x, dl1.y, dl1.z, dl1.w};
-            const float cv[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+            double cv[8];
+#pragma unroll
+            for (int a = 0; a < 8; ++a)
+                cv[a] = sh.key[w][0][8 * j + a] * (IsBF16<CODE>::value ? 1.0 : (double)sh.smooth[8 * kb + a]);
+            // where the 8 codes lie in a row (the 6-bit ones may cross a chunk)
+            uint32_t zoff[CODE == 3 ? 3 : 1];
+#pragma unroll
+            for (int e = 0; e < (CODE == 3 ? 3 : 1); ++e) {
+                const uint32_t y = CodeFmt<CODE>::BITS * kb + 2 * e;
+                zoff[e] = 16 * ((y / 16 + i) % SEGS) + (y & 15);
+            }
 #pragma unroll
             for (int b = 0; b < VPT; ++b) {
-#pragma unroll
-                for (int a = 0; a < 8; ++a) {
-                    const double zf = code8_value<CODE>(zp[b], a);
-                    m[a][b] = (double)cv[a] * (zf * (double)dv[b]);
+                const int v = VPT * i + b;
+                typename Codes8<CODE>::type z;
+                const uint8_t *zr = (const uint8_t *)&sh.codes[v * SEGS];
+                if constexpr (CODE <= 1) {
+                    z = *(const uint2 *)(zr + zoff[0]);
+                } else if constexpr (CODE == 2) {
+                    z = make_uint2(*(const uint32_t *)(zr + zoff[0]), 0u);
+                } else if constexpr (CODE == 3) {
+                    z = make_uint2(*(const uint16_t *)(zr + zoff[0]) | ((uint32_t) * (const uint16_t *)(zr + zoff[1]) << 16),
+                                   *(const uint16_t *)(zr + zoff[2]));
+                } else {
+                    z = load_codes8<CODE>(A.codes, tile, v, kb);
                 }
+                const double dv = IsBF16<CODE>::value ? 1.0 : (double)sh.scale[v];
+#pragma unroll
+                for (int a = 0; a < 8; ++a) M(a, b) = fma(cv[a], code8_value<CODE>(z, a) * dv, M(a, b));
+                __builtin_amdgcn_sched_barrier(0);      // one row's codes live at a time beside the block
             }
-        }
-        // + its compensators K~ U~^T
-        if (ts < r) {
-            float kv[8], uv[8];
-            unpack_h8(ck, kv);
-            unpack_h8(cu, uv);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                sh.key[ts][KP(l16, j)] = (double)kv[j];
-                sh.val[ts][8 * l16 + j] = uv[j];
-            }
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int h = 0; h < r; ++h) {
-            refresh();
-            double ud[VPT];
-#pragma unroll
-            for (int b = 0; b < VPT; ++b) ud[b] = (double)sh.val[h][VPT * vb + b];
-#pragma unroll
-            for (int a = 0; a < 8; ++a) {
-                const double kd = sh.key[h][KP(kb, a)];
-#pragma unroll
-                for (int b = 0; b < VPT; ++b) m[a][b] = fma(kd, ud[b], m[a][b]);
-            }
-        }
-        wait_vm_all();          // the first pass's records have landed in LDS
-        __syncthreads();
-
-        // Each pass: m <- Gamma_pass * m + sum_j Gamma_{j+1:hi} k~_j u_j^T, the
-        // window recursion taken TCH records at a time; within the pass the
-        // decay of every later record is an exclusive suffix product.
-        for (int lo = 0; lo < p; lo += TCH) {
-            refresh();
-            const int hi = lo + TCH < p ? lo + TCH : p;
-            const bool mine = lo + ts < hi;
-            // the record (copied into LDS by this same thread) stays packed in
-            // registers; halves are converted where stored
-            uint4 rk = make_uint4(0, 0, 0, 0), ru = rk, ra = rk;
-            if (mine) {
-                rk = raw[0][ts][l16];
-                ru = raw[1][ts][l16];
-                if (GATE) ra = raw[2][ts][l16];
-                else ra.x = ras;
-            }
-            auto h8 = [](const uint4 &w, int j) {
-                const uint32_t x = j < 2 ? w.x : j < 4 ? w.y : j < 6 ? w.z : w.w;
-                return h2f((uint16_t)(x >> (16 * (j & 1))));
-            };
-            if (GATE) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) sh.bp[ts][KP(l16, j)] = mine ? h8(ra, j) : 1.0f;
-            } else if (l16 == 0) {
-                sh.bp[ts][0] = mine ? h2f((uint16_t)ra.x) : 1.0f;
-            }
-            __syncthreads();
-            if (tid < D) {
-                const int ch = GATE ? tid : 0;
-                double c = 1.0;
-#pragma unroll
-                for (int sl = TCH - 1; sl >= 0; --sl) {
-                    const float bv = sh.bp[sl][ch];
-                    if (GATE || tid == 0) sh.pre[sl][ch] = c;
-                    c *= (double)bv;
-                }
-                if (GATE || tid == 0) sh.tot[ch] = c;
-            }
-            __syncthreads();
-            if (mine) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const double P = sh.pre[ts][GATE ? KP(l16, j) : 0];
-                    sh.key[ts][KP(l16, j)] = P * (double)h8(rk, j);
-                    sh.val[ts][8 * l16 + j] = h8(ru, j);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    sh.key[ts][KP(l16, j)] = 0.0;
-                    sh.val[ts][8 * l16 + j] = 0.0f;
-                }
-            }
-#pragma unroll
-            for (int a = 0; a < 8; ++a) {
-                const double T = sh.tot[GATE ? KP(kb, a) : 0];
-#pragma unroll
-                for (int b = 0; b < VPT; ++b) m[a][b] *= T;
-            }
-            __syncthreads();
-            // sh.pre has been read by every thread: the next pass may land there
-            if (hi < p) load_pass(hi, hi + TCH < p ? hi + TCH : p);
-            // one record at a time, one key channel at a time, so only the
-            // record's 8 values and one key are live beside the block
-            const int nrec = hi - lo;
-            // this lane's parts of the staging addresses, held across the pass
-            refresh();
-            const float *vrow = &sh.val[0][VPT * vb];
-            const double *krow = &sh.key[0][kb];
-#pragma unroll 1
-            for (int j = 0; j < nrec; ++j) {
-                double u0[VPT];
-#pragma unroll
-                for (int b = 0; b < VPT; ++b) u0[b] = (double)vrow[j * D + b];
-#pragma unroll
-                for (int a = 0; a < 8; ++a) {
-                    const double k0 = krow[j * D + 16 * a];
-#pragma unroll
-                    for (int b = 0; b < VPT; ++b) m[a][b] = fma(k0, u0[b], m[a][b]);
-                }
-            }
-            wait_vm_all();      // the next pass's records have landed in LDS
-            __syncthreads();
         }
 
         if (MODE == TILE_DEQUANT) {
             float *S = A.S_out + (size_t)tile * D * D;
 #pragma unroll
             for (int b = 0; b < VPT; ++b) {
-                float4 *row = (float4 *)(S + (size_t)(VPT * vb + b) * D + 8 * kb);
-                row[0] = make_float4((float)m[0][b], (float)m[1][b], (float)m[2][b], (float)m[3][b]);
-                row[1] = make_float4((float)m[4][b], (float)m[5][b], (float)m[6][b], (float)m[7][b]);
+                float4 *row = (float4 *)(S + (size_t)(VPT * i + b) * D + 8 * kb);
+                row[0] = make_float4((float)M(0, b), (float)M(1, b), (float)M(2, b), (float)M(3, b));
+                row[1] = make_float4((float)M(4, b), (float)M(5, b), (float)M(6, b), (float)M(7, b));
             }
             return;
         }
+        __syncthreads();                            // the fit reuses this LDS
+        pin();
     }
 
     // ------------------------------------------------------------------ quantize
+    // y[b] = sum over this thread's key channels of M x, x by lane of the row
+    auto keys_dot = [&](double x, double *y) {
+        const double x0 = row_lane(x, 0);
+#pragma unroll
+        for (int b = 0; b < VPT; ++b) y[b] = M(0, b) * x0;
+#pragma unroll
+        for (int a = 1; a < 8; ++a) {
+            const double xa = row_lane(x, a);
+#pragma unroll
+            for (int b = 0; b < VPT; ++b) y[b] = fma(M(a, b), xa, y[b]);
+        }
+    };
+    int buf = 0;
+#pragma unroll 1
     for (int h = 0; h < r; ++h) {
         refresh();
-        // start vector: key-row l2 norms of the current residual
+        // start vector: key-row l2 norms of the current residual.  A vector over
+        // key channels lives in registers: lane i of a row holds channel i & 7 of
+        // the row's block.
+        double x;
+        {
+            double s[8];
+#pragma unroll
+            for (int a = 0; a < 8; ++a) {
+                s[a] = M(a, 0) * M(a, 0);
+#pragma unroll
+                for (int b = 1; b < VPT; ++b) s[a] = fma(M(a, b), M(a, b), s[a]);
+            }
+            const double n2 = sum_values(sh, s, tid);
+            x = sqrt(n2);
+            const double z = wave_sum_half(n2);
+            if ((tid & 63) == 0) sh.nrm[buf][w] = z;    // |M|_F^2, read after the first sweep's barrier
+        }
+        // Sweeps without normalisation: each is scaled by the power of two
+        // sc ~ 1/|M|_F^2 (exact, so only the direction matters), the first also by
+        // one near 1/|x|, and the vector is normalised once after the last.  A
+        // sweep grows the norm by at most sc*sigma_1^2 < 2.
+        double sc = 0.0;
+#pragma unroll 1
+        for (int it = 0; it < A.power_iters; ++it) {
+            refresh();
+            double y[VPT];
+            keys_dot(x, y);
+            double2 t = sum_keys(sh, y, buf, tid);           // y_v = sum_k M_kv x_k
+            double f = sc;
+            if (it == 0) {
+                const double n2 = sum_nrm(sh, buf);
+                const int e = ilogb(n2);
+                sc = n2 > 0.0 ? ldexp(1.0, -e) : 0.0;
+                f = n2 > 0.0 ? ldexp(sc, -(e >> 1)) : 0.0;
+            }
+            buf ^= 1;
+            t.x *= f;
+            t.y *= f;
+            share_pairs(sh, t, y, tid);
+            double s[8];
+#pragma unroll
+            for (int a = 0; a < 8; ++a) {
+                s[a] = M(a, 0) * y[0];
+#pragma unroll
+                for (int b = 1; b < VPT; ++b) s[a] = fma(M(a, b), y[b], s[a]);
+            }
+            x = sum_values(sh, s, tid);                      // x_k = sum_v M_kv y_v
+        }
+        refresh();
+        {
+            const double z = wave_sum_half(x * x);
+            if ((tid & 63) == 0) sh.nrm[buf][w] = z;
+            __syncthreads();
+            const double nrm = sqrt(sum_nrm(sh, buf));
+            buf ^= 1;
+            x = nrm > 0.0 ? x * (1.0 / nrm) : 0.0;      // a zero residual gives a zero pair
+        }
+        // the pair, rounded to FP16 and stored as soon as it is known
+        const uint16_t kh = d2h_via_f32(x);             // rounded through fp32
+        if (i < 8) A.comp_k[((size_t)tile * r + h) * D + 8 * kb + i] = kh;
+        double kd = (double)h2f(kh);
+        double us[VPT];
+        keys_dot(kd, us);
+        const double2 t = sum_keys(sh, us, buf, tid);        // u~_v = fp16(sum_k M_kv k~_k)
+        buf ^= 1;
+        const uint16_t u0 = d2h_via_f32(t.x), u1 = d2h_via_f32(t.y);
+        if (w == (h & 3))
+            *(uint32_t *)(A.comp_u + ((size_t)tile * r + h) * D + 8 * i + 2 * j) = (uint32_t)u0 | ((uint32_t)u1 << 16);
+        share_pairs(sh, make_double2((double)h2f(u0), (double)h2f(u1)), us, tid);
+        asm volatile("" : "+v"(kd));                    // (its eight lanes are taken again, not held)
 #pragma unroll
         for (int a = 0; a < 8; ++a) {
-            double s = 0.0;
+            const double ka = row_lane(kd, a);
 #pragma unroll
-            for (int b = 0; b < VPT; ++b) s = fma(m[a][b], m[a][b], s);
-            put_part(sh, a, s, kb, vb);
-        }
-        double x = sqrt(sum_parts(sh));
-        double nrm = sqrt(publish(sh, x, true));
-        bool ok = nrm > 0.0;
-        // the published vector is read as sh.vec * xs: 1 / |x| after a
-        // normalisation, 1 between sweeps
-        double xs = ok ? 1.0 / nrm : 0.0;
-        // Sweeps without per-sweep normalisation: each sweep is scaled by the
-        // power of two sc ~ 1/|M|_F^2 (exact, so only the direction matters)
-        // and the vector is normalised once after the last sweep.  A sweep
-        // grows the norm by at most sc*sigma_1^2 < 2.
-        const double sc = ok ? ldexp(1.0, -ilogb(nrm * nrm)) : 0.0;
-        for (int it = 0; ok && it < A.power_iters; ++it) {
-            refresh();
-            // the eight reads of x issued together (one LDS round trip, not
-            // one per pair of channels)
-            double xv[8];
-#pragma unroll
-            for (int a = 0; a < 8; ++a) xv[a] = sh.vec[KP(kb, a)];
-            asm volatile("" : "+v"(xv[0]), "+v"(xv[1]), "+v"(xv[2]), "+v"(xv[3]), "+v"(xv[4]), "+v"(xv[5]),
-                         "+v"(xv[6]), "+v"(xv[7]));
-            double y[VPT];
-#pragma unroll
-            for (int b = 0; b < VPT; ++b) y[b] = m[0][b] * xv[0];
-#pragma unroll
-            for (int a = 1; a < 8; ++a)
-#pragma unroll
-                for (int b = 0; b < VPT; ++b) y[b] = fma(m[a][b], xv[a], y[b]);
-            row_sum8(sh, y, kb, vb, sc * xs);       // y_v = sc * sum_k M_kv (xs x_k)
-#pragma unroll
-            for (int a = 0; a < 8; ++a) {
-                double s = 0.0;
-#pragma unroll
-                for (int b = 0; b < VPT; ++b) s = fma(m[a][b], y[b], s);
-                put_part(sh, a, s, kb, vb);
-            }
-            x = sum_parts(sh);                      // x_k = sum_v M_kv y_v
-            if (it + 1 < A.power_iters) {
-                publish(sh, x, false);
-                xs = 1.0;
-            } else {
-                nrm = sqrt(publish(sh, x, true));
-                ok = nrm > 0.0;
-                xs = ok ? 1.0 / nrm : 0.0;
-            }
-        }
-        // the pair, FP16 bits packed two per word (zero when the residual is zero)
-        // the pair, FP16 bits packed two per word, stored as soon as it is known
-        // (zero when the residual is zero)
-        refresh();
-        if (ok) {
-            float kf[8];
-            uint32_t kw[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int a = 0; a < 8; ++a) {
-                const uint16_t kh = d2h_via_f32(sh.vec[KP(kb, a)] * xs);   // rounded through fp32
-                kw[a >> 1] |= (uint32_t)kh << (16 * (a & 1));
-                kf[a] = h2f(kh);
-            }
-            if (vb == 0)
-                *(uint4 *)(A.comp_k + ((size_t)tile * r + h) * D + 8 * kb) = make_uint4(kw[0], kw[1], kw[2], kw[3]);
-            double us[VPT];
-#pragma unroll
-            for (int b = 0; b < VPT; ++b) {
-                double s = 0.0;
-#pragma unroll
-                for (int a = 0; a < 8; ++a) s = fma(m[a][b], (double)kf[a], s);
-                us[b] = s;
-            }
-            row_sum8(sh, us, kb, vb, 1.0);
-            float uf[VPT];
-            uint32_t uw[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int b = 0; b < VPT; ++b) {
-                const uint16_t uh = d2h_via_f32(us[b]);      // u~_v = fp16(sum_k M_kv k~_k)
-                uw[b >> 1] |= (uint32_t)uh << (16 * (b & 1));
-                uf[b] = h2f(uh);
-            }
-            refresh();
-            if (kb == 0)
-                *(uint4 *)(A.comp_u + ((size_t)tile * r + h) * D + VPT * vb) = make_uint4(uw[0], uw[1], uw[2], uw[3]);
-#pragma unroll
-            for (int a = 0; a < 8; ++a)
-#pragma unroll
-                for (int b = 0; b < VPT; ++b) m[a][b] = fma(-(double)kf[a], (double)uf[b], m[a][b]);
-        } else {
-            if (vb == 0)
-                *(uint4 *)(A.comp_k + ((size_t)tile * r + h) * D + 8 * kb) = make_uint4(0u, 0u, 0u, 0u);
-            if (kb == 0)
-                *(uint4 *)(A.comp_u + ((size_t)tile * r + h) * D + VPT * vb) = make_uint4(0u, 0u, 0u, 0u);
+            for (int b = 0; b < VPT; ++b) M(a, b) = fma(-ka, us[b], M(a, b));
         }
     }
+    refresh();
 
     if constexpr (IsBF16<CODE>::value) {
         // BF16 state: every entry rounded to nearest even through fp32 (the
         // window-end rounding of the per-window BF16 variant), unit scales
-        refresh();
         constexpr int ROW = D * 2;
 #pragma unroll
         for (int b = 0; b < VPT; ++b) {
-            uint32_t w[4];
+            uint32_t o[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                w[e] = (uint32_t)f2bf((float)m[2 * e][b]) | ((uint32_t)f2bf((float)m[2 * e + 1][b]) << 16);
-            *(uint4 *)(A.codes + ((size_t)tile * D + VPT * vb + b) * ROW + 16 * kb) = make_uint4(w[0], w[1], w[2], w[3]);
+                o[e] = (uint32_t)f2bf((float)M(2 * e, b)) | ((uint32_t)f2bf((float)M(2 * e + 1, b)) << 16);
+            *(uint4 *)(A.codes + ((size_t)tile * D + VPT * i + b) * ROW + 16 * kb) = make_uint4(o[0], o[1], o[2], o[3]);
         }
         if (tid < D) {
             A.smooth[tvec + tid] = 1.0f;
@@ -564,56 +619,81 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
         if (tid == 0) A.rec_len[tile] = 0;
         return;
     }
-    refresh();
     // residual smoothing over key rows: c_k = sqrt(max(mean_v |R_kv|, 1e-12)) in fp32
+    float ic[8];
     {
+        double s[8];
 #pragma unroll
         for (int a = 0; a < 8; ++a) {
-            double s = 0.0;
+            s[a] = fabs(M(a, 0));
 #pragma unroll
-            for (int b = 0; b < VPT; ++b) s += fabs(m[a][b]);
-            put_part(sh, a, s, kb, vb);
+            for (int b = 1; b < VPT; ++b) s[a] += fabs(M(a, b));
         }
-        const double s = sum_parts(sh);
+        const double z = sum_values(sh, s, tid);
         float c = 1.0f;
-        if (A.smooth_on) c = (float)sqrt(fmax(s * (1.0 / (double)D), (double)1e-12f));
-        if (tid < D) A.smooth[tvec + KCH(tid)] = c;
-        publish(sh, (double)c, false);
+        if (A.smooth_on) c = (float)sqrt(fmax(z * (1.0 / (double)D), (double)1e-12f));
+        if (i < 8) A.smooth[tvec + 8 * kb + i] = c;
+        const float rc = 1.0f / c;
+#pragma unroll
+        for (int a = 0; a < 8; ++a) ic[a] = row_lane(rc, a);
     }
     refresh();
-    // per-value-channel scale and codes, decided in fp32
+    // per-value-channel scale and codes, decided in fp32.  Lane (row j, i) has the
+    // largest |R^C| of channels 8 i + 2 j, 8 i + 2 j + 1 over its wave's keys.
     constexpr float QMAX = CodeFmt<CODE>::QMAX;
-    float ic[8];
+    float inv[VPT];
+    {
+        float am[VPT];
 #pragma unroll
-    for (int a = 0; a < 8; ++a) ic[a] = 1.0f / (float)sh.vec[KP(kb, a)];
+        for (int b = 0; b < VPT; ++b) {
+            am[b] = fabsf((float)M(0, b) * ic[0]);
+#pragma unroll
+            for (int a = 1; a < 8; ++a) am[b] = fmaxf(am[b], fabsf((float)M(a, b) * ic[a]));
+        }
+        float a0, a1;
+        rows4_max_scatter(am, a0, a1);
+        const int lane = tid & 63;
+        float2 *part = (float2 *)sh.part[buf];
+        part[64 * w + lane] = make_float2(a0, a1);
+        __syncthreads();
+        float2 q[NW];
+#pragma unroll
+        for (int x = 0; x < NW; ++x) q[x] = part[64 * x + lane];
+        a0 = fmaxf(fmaxf(q[0].x, q[1].x), fmaxf(q[2].x, q[3].x));
+        a1 = fmaxf(fmaxf(q[0].y, q[1].y), fmaxf(q[2].y, q[3].y));
+        if (w == 0)
+            *(float2 *)(A.scale + tvec + VPT * i + 2 * j) =
+                make_float2(a0 > 0.0f ? a0 / QMAX : 0.0f, a1 > 0.0f ? a1 / QMAX : 0.0f);
+        float *vec = (float *)sh.vec[w];
+        __builtin_amdgcn_wave_barrier();
+        *(float2 *)&vec[2 * lane] = make_float2(a0 > 0.0f ? QMAX / a0 : 0.0f, a1 > 0.0f ? QMAX / a1 : 0.0f);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const float2 y = *(const float2 *)&vec[32 * x + 2 * i];
+            inv[2 * x] = y.x;
+            inv[2 * x + 1] = y.y;
+        }
+    }
 #pragma unroll
     for (int b = 0; b < VPT; ++b) {
-        float rc[8];
-        float amax = 0.0f;
-#pragma unroll
-        for (int a = 0; a < 8; ++a) {
-            rc[a] = (float)m[a][b] * ic[a];
-            amax = fmaxf(amax, fabsf(rc[a]));
-        }
-        amax = row16_max(amax);
-        const float dl = amax > 0.0f ? amax / QMAX : 0.0f;
-        const float inv = amax > 0.0f ? QMAX / amax : 0.0f;
         uint32_t c8[8];
 #pragma unroll
         for (int a = 0; a < 8; ++a) {
+            const float rc = (float)M(a, b) * ic[a];
             if (CODE == 1) {
-                const float t = fminf(fmaxf(rc[a] * inv, -QMAX), QMAX);
+                const float t = fminf(fmaxf(rc * inv[b], -QMAX), QMAX);
                 c8[a] = f_to_e4m3(t);
             } else {
-                const float t = fminf(fmaxf(rintf(rc[a] * inv), -QMAX), QMAX);
+                const float t = fminf(fmaxf(rintf(rc * inv[b]), -QMAX), QMAX);
                 c8[a] = (uint32_t)(int32_t)t;
             }
         }
-        store_codes8<CODE>(A.codes, tile, VPT * vb + b, kb, encode8<CODE>(c8));
-        if (kb == 0) A.scale[tvec + VPT * vb + b] = dl;
+        store_codes8<CODE>(A.codes, tile, VPT * i + b, kb, encode8<CODE>(c8));
     }
     if (tid == 0) A.rec_len[tile] = 0;
 }
+#undef M
 
 inline TileArgs tile_args(const lq_dims &d, const StatePtrs &s, const float *S_in, float *S_out,
                           const int32_t *mask) {
