@@ -54,10 +54,15 @@ class lq_state(C.Structure):
 
 
 _L = None
+# the native marshalling of regular calls (py_csrc/marshal.cpp) and the addresses
+# of the entry points it calls
+_M = None
+_FN = {"leapquant_decode_step": 0, "leapquant_decode_step_general": 0, "leapquant_decode_step_commit": 0,
+       "leapquant_window_commit": 0}
 
 
 def _lib():
-    global _L
+    global _L, _M
     if _L is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} is missing: build it with paper_2609_38166_amd/build.py "
@@ -81,7 +86,15 @@ def _lib():
         for n in EXPORTS:
             if n not in ("leapquant_strerror", "leapquant_last_hip_error"):
                 getattr(L, n).restype = C.c_int32
-        _L = L
+        marshal_path = os.path.join(_PKG, "_marshal.so")
+        if not os.path.exists(marshal_path):
+            raise ImportError(f"{marshal_path} is missing: build it with paper_2609_38166_amd/build.py")
+        from . import _marshal
+        addr = {n: C.cast(getattr(L, n), vp).value for n in EXPORTS}
+        _marshal.setup(lq_dims, State, FIELDS, addr["leapquant_state_bytes"])
+        for n in _FN:
+            _FN[n] = addr[n]
+        _M, _L = _marshal, L
     return _L
 
 
@@ -233,6 +246,10 @@ def leapquant_quantize_state(dims: lq_dims, S: torch.Tensor, st: State, stream=N
 
 
 def leapquant_decode_step(dims: lq_dims, st: State, q, k, v, alpha, beta, o, stream=None):
+    if stream is None and (_M or _lib()):
+        status = _M.step(_FN["leapquant_decode_step"], dims, st, q, k, v, alpha, beta, o)
+        if status is not None:
+            return _check(status, "leapquant_decode_step")
     _check_state(dims, st)
     _check_tokens(dims, q, k, v, alpha, beta, o)
     s = st.struct()
@@ -244,6 +261,10 @@ def leapquant_decode_step(dims: lq_dims, st: State, q, k, v, alpha, beta, o, str
 def leapquant_decode_step_commit(dims: lq_dims, st: State, q, k, v, alpha, beta, o, stream=None):
     """Decode step, then the commit of every tile whose window it filled, in one
     launch."""
+    if stream is None and (_M or _lib()):
+        status = _M.step(_FN["leapquant_decode_step_commit"], dims, st, q, k, v, alpha, beta, o)
+        if status is not None:
+            return _check(status, "leapquant_decode_step_commit")
     _check_state(dims, st)
     _check_tokens(dims, q, k, v, alpha, beta, o)
     s = st.struct()
@@ -256,6 +277,10 @@ def leapquant_decode_step_general(dims: lq_dims, st: State, q, k, b, v, alpha, b
                                   stream=None):
     """Decode step with the read vectors b [B][heads_v][d_k] given (dims.rule
     must be LQ_RULE_GENERAL)."""
+    if stream is None and (_M or _lib()):
+        status = _M.step_general(_FN["leapquant_decode_step_general"], dims, st, q, k, b, v, alpha, beta, o)
+        if status is not None:
+            return _check(status, "leapquant_decode_step_general")
     _check_state(dims, st)
     _check_tokens(dims, q, k, v, alpha, beta, o)
     _check_read(dims, b)
@@ -267,6 +292,10 @@ def leapquant_decode_step_general(dims: lq_dims, st: State, q, k, b, v, alpha, b
 
 
 def leapquant_window_commit(dims: lq_dims, st: State, mask=None, stream=None):
+    if stream is None and (_M or _lib()):
+        status = _M.commit(_FN["leapquant_window_commit"], dims, st, mask)
+        if status is not None:
+            return _check(status, "leapquant_window_commit")
     _check_state(dims, st)
     if mask is not None:
         _need(mask, dims.batch * 4, "mask")

@@ -19,6 +19,8 @@ ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libleapquant.so")
 # measurement helpers for bench.py (not part of the method's C ABI)
 BENCH_LIB = os.path.join(PKG, "libleapquant_bench.so")
+# argument marshalling of the Python binding (host code, against torch's headers)
+MARSHAL_LIB = os.path.join(PKG, "_marshal.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -70,8 +72,29 @@ def _compile(srcs, out, verbose, defines=()):
     os.replace(tmp, out)
 
 
+def _compile_marshal(verbose):
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    inc = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"], "/opt/rocm/include", *include_paths()]
+    tmp = MARSHAL_LIB + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(x for d in inc for x in ("-isystem", d)),
+           os.path.join(PKG, "py_csrc", "marshal.cpp"), "-o", tmp,
+           "-L", lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), file=sys.stderr)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, MARSHAL_LIB)
+
+
 def build(verbose: bool = False) -> str:
-    _compile(sources(), LIB, verbose)
+    with ThreadPoolExecutor(max_workers=1) as ex:
+        marshal = ex.submit(_compile_marshal, verbose)
+        _compile(sources(), LIB, verbose)
+        marshal.result()
     _compile(sorted(glob.glob(os.path.join(PKG, "bench_csrc", "*.hip"))), BENCH_LIB, verbose)
     return LIB
 
