@@ -16,12 +16,12 @@
 //
 // What bounds it: fp64 issue, and in the sweeps the LDS transposes and the
 // barrier beside it.  A sweep is 128 FMA per lane (0.27 us per tile and CU at the
-// 2.05 GHz that the card holds under them); it takes 0.40 us with three
-// workgroups per CU and 0.73 us with one.  Measured at r = 8, 4 sweeps against
+// 2.05 GHz that the card holds under them); it takes 0.38 us with three
+// workgroups per CU and 0.70 us with one.  Measured at r = 8, 4 sweeps against
 // the layout before (a thread's block in a row of key blocks, two barriers and
-// five LDS round trips a sweep): quantize 48.7 -> 39.7 us for 32 tiles, 1578 ->
-// 1455 us for 16384; commit of 64 records (per-channel gate) 75.6 -> 57.3 us
-// for 32 tiles, 182 -> 160 us for 1024, 1245 -> 1110 us for 8192.
+// five LDS round trips a sweep): quantize 48.6 -> 37.3 us for 32 tiles, 1543 ->
+// 1374 us for 16384; commit of 64 records (per-channel gate) 75.6 -> 55.3 us
+// for 32 tiles, 182 -> 150 us for 1024, 1245 -> 1060 us for 8192.
 //
 // The rank-one terms of the reconstruction (records, Compensator Tokens) go
 // through the fp64 matrix cores, v_mfma_f64_16x16x4: the same rate per cycle as
@@ -202,17 +202,24 @@ __device__ __forceinline__ void share_pairs(TileShared &sh, double2 t, double *v
     __builtin_amdgcn_wave_barrier();
 }
 
-// Sum over value channels of p[a] (a = 0..7: this thread's key channels, its 8
+// Sum over value channels of part(a) (a = 0..7: this thread's key channels, its 8
 // value channels added up) over the 16 lanes of its row, which lie in one
 // wave: a row-private LDS transpose, no barrier.  Lane i receives key channel
 // i & 7.  Channels are 17 words apart: neither the writes (16 lanes of one
-// channel) nor the reads (lane (c, h): 8 lanes of channel c) share a bank.
-__device__ __forceinline__ double sum_values(TileShared &sh, const double *p, int tid) {
+// channel) nor the reads (lane (c, h): 8 lanes of channel c) share a bank.  A
+// partial is stored as soon as it is made, so that the stores run beside the
+// next one's arithmetic (4% off a commit and 6% off a quantization against
+// storing the eight together).
+template <typename F>
+__device__ __forceinline__ double sum_values(TileShared &sh, F part, int tid) {
     const int i = tid & 15, c = i & 7, h = i >> 3;
     double *r = sh.red[tid >> 4];
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int a = 0; a < 8; ++a) r[17 * a + i] = p[a];
+    for (int a = 0; a < 8; ++a) {
+        r[17 * a + i] = part(a);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     __builtin_amdgcn_wave_barrier();
     double s[8];
 #pragma unroll
@@ -526,14 +533,12 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
         // the row's block.
         double x;
         {
-            double s[8];
+            const double n2 = sum_values(sh, [&](int a) {
+                double s = M(a, 0) * M(a, 0);
 #pragma unroll
-            for (int a = 0; a < 8; ++a) {
-                s[a] = M(a, 0) * M(a, 0);
-#pragma unroll
-                for (int b = 1; b < VPT; ++b) s[a] = fma(M(a, b), M(a, b), s[a]);
-            }
-            const double n2 = sum_values(sh, s, tid);
+                for (int b = 1; b < VPT; ++b) s = fma(M(a, b), M(a, b), s);
+                return s;
+            }, tid);
             x = sqrt(n2);
             const double z = wave_sum_half(n2);
             if ((tid & 63) == 0) sh.nrm[buf][w] = z;    // |M|_F^2, read after the first sweep's barrier
@@ -560,23 +565,21 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
             t.x *= f;
             t.y *= f;
             share_pairs(sh, t, y, tid);
-            double s[8];
+            x = sum_values(sh, [&](int a) {             // x_k = sum_v M_kv y_v
+                double s = M(a, 0) * y[0];
 #pragma unroll
-            for (int a = 0; a < 8; ++a) {
-                s[a] = M(a, 0) * y[0];
-#pragma unroll
-                for (int b = 1; b < VPT; ++b) s[a] = fma(M(a, b), y[b], s[a]);
-            }
-            x = sum_values(sh, s, tid);                      // x_k = sum_v M_kv y_v
+                for (int b = 1; b < VPT; ++b) s = fma(M(a, b), y[b], s);
+                return s;
+            }, tid);
         }
         refresh();
         {
             const double z = wave_sum_half(x * x);
             if ((tid & 63) == 0) sh.nrm[buf][w] = z;
             __syncthreads();
-            const double nrm = sqrt(sum_nrm(sh, buf));
+            const double n2 = sum_nrm(sh, buf);
             buf ^= 1;
-            x = nrm > 0.0 ? x * (1.0 / nrm) : 0.0;      // a zero residual gives a zero pair
+            x = n2 > 0.0 ? x * rsqrt(n2) : 0.0;         // a zero residual gives a zero pair
         }
         // the pair, rounded to FP16 and stored as soon as it is known
         const uint16_t kh = d2h_via_f32(x);             // rounded through fp32
@@ -622,14 +625,12 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
     // residual smoothing over key rows: c_k = sqrt(max(mean_v |R_kv|, 1e-12)) in fp32
     float ic[8];
     {
-        double s[8];
+        const double z = sum_values(sh, [&](int a) {
+            double s = fabs(M(a, 0));
 #pragma unroll
-        for (int a = 0; a < 8; ++a) {
-            s[a] = fabs(M(a, 0));
-#pragma unroll
-            for (int b = 1; b < VPT; ++b) s[a] += fabs(M(a, b));
-        }
-        const double z = sum_values(sh, s, tid);
+            for (int b = 1; b < VPT; ++b) s += fabs(M(a, b));
+            return s;
+        }, tid);
         float c = 1.0f;
         if (A.smooth_on) c = (float)sqrt(fmax(z * (1.0 / (double)D), (double)1e-12f));
         if (i < 8) A.smooth[tvec + 8 * kb + i] = c;
