@@ -119,18 +119,6 @@ __device__ __forceinline__ double h2d(uint32_t w, int hi) {
     return (double)h2f((uint16_t)(w >> (16 * hi)));
 }
 
-// Largest value of x over the 64 lanes of the wave (every lane gets it).
-__device__ __forceinline__ int wave_max_i32(int x) {
-    x = max(x, __builtin_amdgcn_update_dpp(0, x, DPP_XOR1, 0xF, 0xF, false));
-    x = max(x, __builtin_amdgcn_update_dpp(0, x, DPP_XOR2, 0xF, 0xF, false));
-    x = max(x, __builtin_amdgcn_update_dpp(0, x, DPP_ROR4, 0xF, 0xF, false));
-    x = max(x, __builtin_amdgcn_update_dpp(0, x, DPP_ROR8, 0xF, 0xF, false));
-    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);     // rows rho, rho ^ 2
-    x = max((int)r[0], (int)r[1]);
-    const auto r2 = __builtin_amdgcn_permlane16_swap(x, x, false, false);    // rows rho, rho ^ 1
-    return max((int)r2[0], (int)r2[1]);
-}
-
 // Code rows in LDS are stored in 16-byte chunks, each row rotated by zrot(v)
 // chunks, so that the lanes of one matrix-core operand read (16 consecutive
 // rows at one chunk position) fall in distinct banks.  The rotation is applied

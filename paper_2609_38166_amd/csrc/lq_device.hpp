@@ -142,6 +142,18 @@ __device__ __forceinline__ void rows4_max_scatter(const float *x, float &s0, flo
     s1 = fmaxf(__uint_as_float(r1[0]), __uint_as_float(r1[1]));
 }
 
+// Largest value of x over the 64 lanes of the wave (every lane gets it).
+__device__ __forceinline__ int wave_max_i32(int x) {
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, DPP_XOR1, 0xF, 0xF, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, DPP_XOR2, 0xF, 0xF, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, DPP_ROR4, 0xF, 0xF, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, DPP_ROR8, 0xF, 0xF, false));
+    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);     // rows rho, rho ^ 2
+    x = max((int)r[0], (int)r[1]);
+    const auto r2 = __builtin_amdgcn_permlane16_swap(x, x, false, false);    // rows rho, rho ^ 1
+    return max((int)r2[0], (int)r2[1]);
+}
+
 // 64-bit DPP move: lane n of each 16-lane row to every lane of the row.  (The
 // intrinsic is declared by name: the builtin takes 32-bit values only, and the
 // two 32-bit moves it would need cost twice as much.)

@@ -57,6 +57,8 @@
 #include "lq_device.hpp"
 #include "lq_internal.hpp"
 
+#include <limits.h>
+
 namespace lq {
 
 namespace {
@@ -98,6 +100,8 @@ __device__ __forceinline__ double code8_value(const typename Codes8<CODE>::type 
         return (double)bf2f((uint16_t)(x >> (16 * (a & 1))));
     } else {
         const uint32_t w[2] = {z.x, z.y};
+        if (CODE == 0) return (double)sfield(w[a >> 2], 8 * (a & 3), 8);
+        if (CODE == 2) return (double)sfield(w[0], 4 * a, 4);
         return (double)code_at<CODE>(w, a);
     }
 }
@@ -159,6 +163,7 @@ struct TileShared {
         struct {                            // fit
             double part[2][NW][D];          // per-wave partials of a sum over key channels, two in turn
             double nrm[2][NW];              // per-wave partial squared norms
+            int ex[2][NW];                  // per-wave largest exponent of a squared row norm
             double vec[NW][D];              // a wave's copy of a summed vector (VP order)
             double red[TT / 16][8 * 17];    // row-private transposes of a sum over value channels
         };
@@ -247,12 +252,14 @@ __device__ __forceinline__ T row_lane(T z, int a) {
 
 // Sum over the wave of z, which lanes i and i + 8 of a row both hold.
 __device__ __forceinline__ double wave_sum_half(double z) {
-    z = row16_sum(z);
+    z += dpp<DPP_XOR1>(z);
+    z += dpp<DPP_XOR2>(z);
+    z += dpp<DPP_HALF_MIRROR>(z);
     double a, b;
     swap32_d(z, z, a, b);
     z = a + b;
     swap16_d(z, z, a, b);
-    return 0.5 * (a + b);
+    return a + b;
 }
 
 __device__ __forceinline__ double sum_nrm(const TileShared &sh, int buf) {
@@ -539,14 +546,16 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
                 for (int b = 1; b < VPT; ++b) s = fma(M(a, b), M(a, b), s);
                 return s;
             }, tid);
-            x = sqrt(n2);
-            const double z = wave_sum_half(n2);
-            if ((tid & 63) == 0) sh.nrm[buf][w] = z;    // |M|_F^2, read after the first sweep's barrier
+            x = n2 > 0.0 ? n2 * rsqrt(n2) : 0.0;
+            const int e = wave_max_i32(n2 > 0.0 ? __builtin_amdgcn_frexp_exp(n2) : INT_MIN);
+            if ((tid & 63) == 0) sh.ex[buf][w] = e;     // read after the first sweep's barrier
         }
-        // Sweeps without normalisation: each is scaled by the power of two
-        // sc ~ 1/|M|_F^2 (exact, so only the direction matters), the first also by
-        // one near 1/|x|, and the vector is normalised once after the last.  A
-        // sweep grows the norm by at most sc*sigma_1^2 < 2.
+        // Sweeps without normalisation: each is scaled by one power of two (exact, so
+        // only the direction matters), the first also by one near 1/|x|, and the
+        // vector is normalised once after the last.  With 2^(e-1) <= n < 2^e for the
+        // largest squared row norm n, n <= sigma_1^2 <= |M|_F^2 <= 128 n: a sweep
+        // scaled by 2^-(e+3) changes the norm by a factor in about 2^-4 .. 2^4, far
+        // from the ends of the range for every sweep count.
         double sc = 0.0;
 #pragma unroll 1
         for (int it = 0; it < A.power_iters; ++it) {
@@ -556,10 +565,10 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
             double2 t = sum_keys(sh, y, buf, tid);           // y_v = sum_k M_kv x_k
             double f = sc;
             if (it == 0) {
-                const double n2 = sum_nrm(sh, buf);
-                const int e = ilogb(n2);
-                sc = n2 > 0.0 ? ldexp(1.0, -e) : 0.0;
-                f = n2 > 0.0 ? ldexp(sc, -(e >> 1)) : 0.0;
+                const int e = max(max(sh.ex[buf][0], sh.ex[buf][1]), max(sh.ex[buf][2], sh.ex[buf][3]));
+                const bool any = e != INT_MIN;          // a zero residual: every vector 0
+                sc = any ? ldexp(1.0, -(e + 3)) : 0.0;
+                f = any ? ldexp(sc, -(e >> 1)) : 0.0;
             }
             buf ^= 1;
             t.x *= f;
@@ -643,13 +652,18 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
     // largest |R^C| of channels 8 i + 2 j, 8 i + 2 j + 1 over its wave's keys.
     constexpr float QMAX = CodeFmt<CODE>::QMAX;
     float inv[VPT];
+    float rc[8][VPT];                               // the smoothed residual
+#pragma unroll
+    for (int b = 0; b < VPT; ++b)
+#pragma unroll
+        for (int a = 0; a < 8; ++a) rc[a][b] = (float)M(a, b) * ic[a];
     {
         float am[VPT];
 #pragma unroll
         for (int b = 0; b < VPT; ++b) {
-            am[b] = fabsf((float)M(0, b) * ic[0]);
+            am[b] = fabsf(rc[0][b]);
 #pragma unroll
-            for (int a = 1; a < 8; ++a) am[b] = fmaxf(am[b], fabsf((float)M(a, b) * ic[a]));
+            for (int a = 1; a < 8; ++a) am[b] = fmaxf(am[b], fabsf(rc[a][b]));
         }
         float a0, a1;
         rows4_max_scatter(am, a0, a1);
@@ -681,14 +695,9 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
         uint32_t c8[8];
 #pragma unroll
         for (int a = 0; a < 8; ++a) {
-            const float rc = (float)M(a, b) * ic[a];
-            if (CODE == 1) {
-                const float t = fminf(fmaxf(rc * inv[b], -QMAX), QMAX);
-                c8[a] = f_to_e4m3(t);
-            } else {
-                const float t = fminf(fmaxf(rintf(rc * inv[b]), -QMAX), QMAX);
-                c8[a] = (uint32_t)(int32_t)t;
-            }
+            // (clamped to +-QMAX)
+            if (CODE == 1) c8[a] = f_to_e4m3(__builtin_amdgcn_fmed3f(rc[a][b] * inv[b], -QMAX, QMAX));
+            else c8[a] = (uint32_t)(int32_t)__builtin_amdgcn_fmed3f(rintf(rc[a][b] * inv[b]), -QMAX, QMAX);
         }
         store_codes8<CODE>(A.codes, tile, VPT * i + b, kb, encode8<CODE>(c8));
     }
