@@ -4,8 +4,9 @@
 //
 // One 256-thread workgroup (4 waves) owns one 128 x 128 tile held in
 // registers: wave w owns key channels 32 w .. 32 w + 31, and lane (row j, i) of
-// it the 8 x 8 block M[32 w + 8 j + a][8 i + b] of the state in paper
-// orientation (row = key channel).  A sum over value channels stays inside a
+// it the 8 x 8 block M[32 w + 8 j + a][16 b + i] of the state in paper
+// orientation (row = key channel): a memory instruction of a wave then touches
+// 16 neighbouring rows, not 16 rows 4 KiB apart, which met in few L2 channels.  A sum over value channels stays inside a
 // 16-lane row; a sum over key channels crosses the wave's rows in registers and
 // the waves through LDS: one barrier per power sweep.  A vector over key
 // channels never leaves its wave.  Three workgroups share a CU (166 VGPRs per
@@ -74,24 +75,6 @@ constexpr int VPT = 8;      // value channels per thread
 template <int CODE> struct Codes8 { typedef uint2 type; };
 template <> struct Codes8<4> { typedef uint4 type; };
 
-template <int CODE>
-__device__ __forceinline__ typename Codes8<CODE>::type load_codes8(const uint8_t *codes, int tile, int v, int kb) {
-    constexpr int ROW = D * CodeFmt<CODE>::BITS / 8;
-    const uint8_t *p = codes + ((size_t)tile * D + v) * ROW + kb * CodeFmt<CODE>::BITS;
-    typename Codes8<CODE>::type w;
-    if constexpr (CODE == 4) {
-        w = *(const uint4 *)p;
-    } else if constexpr (CODE <= 1) {
-        w = *(const uint2 *)p;
-    } else if constexpr (CODE == 2) {
-        w = make_uint2(*(const uint32_t *)p, 0u);
-    } else {
-        const uint16_t *h = (const uint16_t *)p;
-        w = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2]);
-    }
-    return w;
-}
-
 // Value a (0..7) of the 8 codes as a double (BF16 state: the value itself).
 template <int CODE>
 __device__ __forceinline__ double code8_value(const typename Codes8<CODE>::type &z, int a) {
@@ -145,18 +128,18 @@ struct TileArgs {
     int smooth_on;
 };
 
-// Codes that the reconstruction copies into LDS when it starts; the BF16 state
-// (32 KiB a tile) is loaded where it is used.
-template <int CODE> struct CodesInLds { static constexpr bool value = !IsBF16<CODE>::value; };
+// Value channels whose codes the reconstruction copies into LDS when it starts:
+// all, or the first half of the BF16 state's 32 KiB.
+template <int CODE> struct CodeRows { static constexpr int value = IsBF16<CODE>::value ? D / 2 : D; };
 
 struct TileShared {
     union {
         struct {                            // reconstruction
             double key[NW][TCH][32];        // a wave's record keys, decay folded in
-            double val[2][TCH][D];          // record values, two passes in turn (channel 8 i + b at 16 b + i)
+            double val[2][TCH][D];          // record values, two passes in turn
             uint4 raw_ka[NW][64];           // copied records: a wave's keys, then decays
             uint4 raw_u[NW][32];            // two records' values of each wave
-            uint4 codes[D * D / 16];        // rows rotated by (v >> 3)
+            uint4 codes[D * D / 16];        // rows rotated by v & 15 chunks
             float scale[D];
             float smooth[D];
         };
@@ -170,7 +153,7 @@ struct TileShared {
     };
 };
 
-// Order of a value vector in LDS: channel v = 8 i + 2 q + e at 32 q + 2 i + e, so
+// Order of a value vector in LDS: channel v = 16 (2 q + e) + i at 32 q + 2 i + e, so
 // the 16 lanes of a row that read pair q of their block touch 256 consecutive
 // bytes, and lane (row j, i) of a wave that holds pair j sits at 2 * lane.
 
@@ -178,7 +161,7 @@ struct TileShared {
 // key channels added up): over the wave's 4 rows by cross-row swaps, over the
 // 4 waves through LDS.  One barrier; `buf` alternates between calls, so a
 // call's writes meet only reads that the previous call's barrier has ended.
-// Lane (row j, i) receives channels 8 i + 2 j and 8 i + 2 j + 1.
+// Lane (row j, i) receives channels 32 j + i and 32 j + 16 + i (b = 2 j, 2 j + 1).
 __device__ __forceinline__ double2 sum_keys(TileShared &sh, const double *v, int buf, int tid) {
     const int lane = tid & 63, w = tid >> 6;
     double s0, s1;
@@ -192,7 +175,7 @@ __device__ __forceinline__ double2 sum_keys(TileShared &sh, const double *v, int
 }
 
 // The lane's pair of a value vector to every lane of the wave: v[b] = channel
-// 8 i + b (through the wave's own LDS copy; no barrier).
+// 16 b + i (through the wave's own LDS copy; no barrier).
 __device__ __forceinline__ void share_pairs(TileShared &sh, double2 t, double *v, int tid) {
     const int lane = tid & 63, w = tid >> 6, i = lane & 15;
     __builtin_amdgcn_wave_barrier();
@@ -291,7 +274,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
     const size_t tvec = (size_t)tile * D;
     const int r = A.n_comp;
 
-    // the block: M(a, b) = M[8 kb + a][8 i + b], in the accumulator layout of
+    // the block: M(a, b) = M[8 kb + a][16 b + i], in the accumulator layout of
     // v_mfma_f64_16x16x4 (accumulator (a >> 2, b): row j + 4 (a & 3), column i)
     v4d m4[2][VPT];
 #define M(a, b) m4[(a) >> 2][b][(a) & 3]
@@ -305,7 +288,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
         const float *S = A.S_in + (size_t)tile * D * D;
 #pragma unroll
         for (int b = 0; b < VPT; ++b) {
-            const float4 *row = (const float4 *)(S + (size_t)(VPT * i + b) * D + 8 * kb);
+            const float4 *row = (const float4 *)(S + (size_t)(16 * b + i) * D + 8 * kb);
             const float4 lo = row[0], hi = row[1];
             M(0, b) = lo.x; M(1, b) = lo.y; M(2, b) = lo.z; M(3, b) = lo.w;
             M(4, b) = hi.x; M(5, b) = hi.y; M(6, b) = hi.z; M(7, b) = hi.w;
@@ -361,21 +344,22 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
             }
         };
         if (passes > 0) load_pass(0);
-        // the base's codes, row v's 16-byte chunk c at chunk (c + (v >> 3)) mod SEGS of
+        // the base's codes, row v's 16-byte chunk c at chunk (c + (v & 15)) mod SEGS of
         // its row: the 16 rows that a read touches then spread over the banks
-        constexpr int SEGS = D * CodeFmt<CODE>::BITS / 8 / 16, NCP = CodesInLds<CODE>::value ? D * SEGS / TT : 0;
+        constexpr int SEGS = D * CodeFmt<CODE>::BITS / 8 / 16, NCP = CodeRows<CODE>::value * SEGS / TT;
         if constexpr (!IsBF16<CODE>::value) {
             if (tid < 32) dma16(A.scale + tvec + 4 * tid, lds_addr(sh.scale));
             if (w == 1 && (tid & 63) < 32) dma16(A.smooth + tvec + 4 * (tid & 63), lds_addr(sh.smooth));
         }
-        if constexpr (CodesInLds<CODE>::value) {
-            const uint4 *zt = (const uint4 *)(A.codes + (size_t)tile * D * SEGS * 16);
+        auto copy_codes = [&](int v0, uint4 *to) {  // rows v0 .. v0 + CodeRows - 1
+            const uint4 *zt = (const uint4 *)(A.codes + ((size_t)tile * D + v0) * (SEGS * 16));
 #pragma unroll
             for (int x = 0; x < NCP; ++x) {
-                const int P = TT * x + tid, v = P / SEGS, c = P % SEGS;
-                dma16(zt + v * SEGS + (c + 16 * SEGS - (v >> 3)) % SEGS, lds_addr(&sh.codes[TT * x + 64 * w]));
+                const int P = TT * x + (int)threadIdx.x, v = P / SEGS, c = P % SEGS;
+                dma16(zt + v * SEGS + (c + 16 * SEGS - (v & 15)) % SEGS, lds_addr(to + TT * x + 64 * w));
             }
-        }
+        };
+        copy_codes(0, sh.codes);
 #pragma unroll
         for (int a = 0; a < 8; ++a)
 #pragma unroll
@@ -434,15 +418,12 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
                     sh.key[w][s0 - e][c] = P * (double)h2f((uint16_t)(s0 - e < n ? rk[e] : 0u));
                     P *= av[e];
                 }
-                // values: lane (record, 4-channel segment) of the wave's two records,
-                // channel 8 i + b at 16 b + i
+                // values: lane (record, 4-channel segment) of the wave's two records
                 const int s = 2 * w + h;
-                double *val = &sh.val[t & 1][s][64 * (c & 1) + (c >> 1)];
+                double *val = &sh.val[t & 1][s][4 * c];
                 const uint32_t u0 = s < n ? u.x : 0u, u1 = s < n ? u.y : 0u;
-                val[0] = (double)h2f((uint16_t)u0);
-                val[16] = (double)h2f((uint16_t)(u0 >> 16));
-                val[32] = (double)h2f((uint16_t)u1);
-                val[48] = (double)h2f((uint16_t)(u1 >> 16));
+                *(double2 *)&val[0] = make_double2((double)h2f((uint16_t)u0), (double)h2f((uint16_t)(u0 >> 16)));
+                *(double2 *)&val[2] = make_double2((double)h2f((uint16_t)u1), (double)h2f((uint16_t)(u1 >> 16)));
             }
             __syncthreads();
             // this wave's raw copies have been read: the next pass may land there
@@ -475,6 +456,9 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
 #pragma unroll
             for (int a = 0; a < 8; ++a)
                 cv[a] = sh.key[w][0][8 * j + a] * (IsBF16<CODE>::value ? 1.0 : (double)sh.smooth[8 * kb + a]);
+            // (the record values are no longer read: the BF16 state's second half lands there
+            // beside the first half's arithmetic)
+            if constexpr (IsBF16<CODE>::value) copy_codes(D / 2, (uint4 *)sh.val);
             // where the 8 codes lie in a row (the 6-bit ones may cross a chunk)
             uint32_t zoff[CODE == 3 ? 3 : 1];
 #pragma unroll
@@ -484,9 +468,14 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
             }
 #pragma unroll
             for (int b = 0; b < VPT; ++b) {
-                const int v = VPT * i + b;
+                const int v = 16 * b + i;
                 typename Codes8<CODE>::type z;
-                const uint8_t *zr = (const uint8_t *)&sh.codes[v * SEGS];
+                if (16 * b == CodeRows<CODE>::value) {
+                    wait_vm_all();
+                    __syncthreads();
+                }
+                const uint4 *zv = 16 * b < CodeRows<CODE>::value ? sh.codes : (const uint4 *)sh.val;
+                const uint8_t *zr = (const uint8_t *)&zv[(v & (CodeRows<CODE>::value - 1)) * SEGS];
                 if constexpr (CODE <= 1) {
                     z = *(const uint2 *)(zr + zoff[0]);
                 } else if constexpr (CODE == 2) {
@@ -495,7 +484,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
                     z = make_uint2(*(const uint16_t *)(zr + zoff[0]) | ((uint32_t) * (const uint16_t *)(zr + zoff[1]) << 16),
                                    *(const uint16_t *)(zr + zoff[2]));
                 } else {
-                    z = load_codes8<CODE>(A.codes, tile, v, kb);
+                    z = *(const uint4 *)(zr + zoff[0]);
                 }
                 const double dv = IsBF16<CODE>::value ? 1.0 : (double)sh.scale[v];
 #pragma unroll
@@ -508,7 +497,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
             float *S = A.S_out + (size_t)tile * D * D;
 #pragma unroll
             for (int b = 0; b < VPT; ++b) {
-                float4 *row = (float4 *)(S + (size_t)(VPT * i + b) * D + 8 * kb);
+                float4 *row = (float4 *)(S + (size_t)(16 * b + i) * D + 8 * kb);
                 row[0] = make_float4((float)M(0, b), (float)M(1, b), (float)M(2, b), (float)M(3, b));
                 row[1] = make_float4((float)M(4, b), (float)M(5, b), (float)M(6, b), (float)M(7, b));
             }
@@ -599,8 +588,11 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
         const double2 t = sum_keys(sh, us, buf, tid);        // u~_v = fp16(sum_k M_kv k~_k)
         buf ^= 1;
         const uint16_t u0 = d2h_via_f32(t.x), u1 = d2h_via_f32(t.y);
-        if (w == (h & 3))
-            *(uint32_t *)(A.comp_u + ((size_t)tile * r + h) * D + 8 * i + 2 * j) = (uint32_t)u0 | ((uint32_t)u1 << 16);
+        if (w == (h & 3)) {
+            uint16_t *cu = A.comp_u + ((size_t)tile * r + h) * D + 32 * j + i;
+            cu[0] = u0;
+            cu[16] = u1;
+        }
         share_pairs(sh, make_double2((double)h2f(u0), (double)h2f(u1)), us, tid);
         asm volatile("" : "+v"(kd));                    // (its eight lanes are taken again, not held)
 #pragma unroll
@@ -622,7 +614,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 o[e] = (uint32_t)f2bf((float)M(2 * e, b)) | ((uint32_t)f2bf((float)M(2 * e + 1, b)) << 16);
-            *(uint4 *)(A.codes + ((size_t)tile * D + VPT * i + b) * ROW + 16 * kb) = make_uint4(o[0], o[1], o[2], o[3]);
+            *(uint4 *)(A.codes + ((size_t)tile * D + 16 * b + i) * ROW + 16 * kb) = make_uint4(o[0], o[1], o[2], o[3]);
         }
         if (tid < D) {
             A.smooth[tvec + tid] = 1.0f;
@@ -649,7 +641,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
     }
     refresh();
     // per-value-channel scale and codes, decided in fp32.  Lane (row j, i) has the
-    // largest |R^C| of channels 8 i + 2 j, 8 i + 2 j + 1 over its wave's keys.
+    // largest |R^C| of channels 32 j + i, 32 j + 16 + i over its wave's keys.
     constexpr float QMAX = CodeFmt<CODE>::QMAX;
     float inv[VPT];
     float rc[8][VPT];                               // the smoothed residual
@@ -676,9 +668,10 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
         for (int x = 0; x < NW; ++x) q[x] = part[64 * x + lane];
         a0 = fmaxf(fmaxf(q[0].x, q[1].x), fmaxf(q[2].x, q[3].x));
         a1 = fmaxf(fmaxf(q[0].y, q[1].y), fmaxf(q[2].y, q[3].y));
-        if (w == 0)
-            *(float2 *)(A.scale + tvec + VPT * i + 2 * j) =
-                make_float2(a0 > 0.0f ? a0 / QMAX : 0.0f, a1 > 0.0f ? a1 / QMAX : 0.0f);
+        if (w == 0) {
+            A.scale[tvec + 32 * j + i] = a0 > 0.0f ? a0 / QMAX : 0.0f;
+            A.scale[tvec + 32 * j + 16 + i] = a1 > 0.0f ? a1 / QMAX : 0.0f;
+        }
         float *vec = (float *)sh.vec[w];
         __builtin_amdgcn_wave_barrier();
         *(float2 *)&vec[2 * lane] = make_float2(a0 > 0.0f ? QMAX / a0 : 0.0f, a1 > 0.0f ? QMAX / a1 : 0.0f);
@@ -699,7 +692,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
             if (CODE == 1) c8[a] = f_to_e4m3(__builtin_amdgcn_fmed3f(rc[a][b] * inv[b], -QMAX, QMAX));
             else c8[a] = (uint32_t)(int32_t)__builtin_amdgcn_fmed3f(rintf(rc[a][b] * inv[b]), -QMAX, QMAX);
         }
-        store_codes8<CODE>(A.codes, tile, VPT * i + b, kb, encode8<CODE>(c8));
+        store_codes8<CODE>(A.codes, tile, 16 * b + i, kb, encode8<CODE>(c8));
     }
     if (tid == 0) A.rec_len[tile] = 0;
 }
