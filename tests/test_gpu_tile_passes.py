@@ -46,3 +46,30 @@ def test_partial_passes(gate, r, code):
     want = [O.quantize(cfg, x) for x in exp]
     for f in ("Z", "delta", "c", "Kt", "Ut"):                    # decided from sums in fp64, as the oracle's
         assert np.array_equal(rep[f], np.stack([getattr(x, f) for x in want])), f
+
+
+@pytest.mark.parametrize("code", [synth.CODE_INT8, synth.CODE_INT6])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf"), None])
+def test_a_residual_without_a_direction_gives_zero_pairs(bad, code):
+    """A state that holds a NaN or an infinity, or only zeros (None, of either sign), has zero tokens: what remains
+    is its plain quantization, and its other value channels stay finite."""
+    S = torch.randn((2, 1, 128, 128), generator=torch.Generator().manual_seed(3)).cuda()     # S^T: [value][key]
+    if bad is None:
+        S[1] = -torch.zeros_like(S[1])
+    else:
+        S[1, 0, 17, 70] = bad
+    st = {}
+    for r in (0, 3):
+        d = B.make_dims(2, 1, 1, window=4, n_comp=r, code=code)
+        st[r] = B.State.empty(d)
+        B.leapquant_quantize_state(d, S, st[r])
+    for x in (st[3].comp_k, st[3].comp_u):
+        assert x[0].view(torch.int16).any() and not x[1].view(torch.int16).any()
+    for f in ("codes", "scale", "smooth"):
+        a, b = (getattr(st[r], f)[1].view(torch.uint8) for r in (0, 3))
+        assert torch.equal(a, b), f
+    out = torch.empty_like(S)
+    B.leapquant_dequantize_state(d, st[3], out)
+    rest = [v for v in range(128) if v != 17]
+    keys = [k for k in range(128) if k != 70]            # (an infinite row has an infinite smoothing scale)
+    assert torch.isfinite(out[1, 0, rest][:, keys]).all()
