@@ -571,15 +571,16 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
             }, tid);
         }
         refresh();
-        bool ok;                                        // uniform
+        uint32_t keep;                                  // all ones, or 0 for a zero pair (in a scalar register)
         {
             const double z = wave_sum_half(x * x);
             if ((tid & 63) == 0) sh.nrm[buf][w] = z;
             __syncthreads();
             const double n2 = sum_nrm(sh, buf);
             buf ^= 1;
-            ok = n2 > 0.0;                              // a zero or non-finite residual gives a zero pair
-            x = ok ? x * rsqrt(n2) : 0.0;
+            x = n2 > 0.0 ? x * rsqrt(n2) : 0.0;         // a zero or non-finite residual gives a zero pair
+            keep = __builtin_amdgcn_readfirstlane(n2 > 0.0 ? 0xFFFFu : 0u);
+            asm volatile("" : "+s"(keep));
         }
         // the pair, rounded to FP16 and stored as soon as it is known
         const uint16_t kh = d2h_via_f32(x);             // rounded through fp32
@@ -589,9 +590,9 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
         keys_dot(kd, us);
         const double2 t = sum_keys(sh, us, buf, tid);        // u~_v = fp16(sum_k M_kv k~_k)
         buf ^= 1;
-        // (0 times an infinity or a NaN is no zero: u~ of a zero pair is set, so that the
-        // entries beside a non-finite one stay what they are)
-        const uint16_t u0 = ok ? d2h_via_f32(t.x) : 0, u1 = ok ? d2h_via_f32(t.y) : 0;
+        // (0 times an infinity or a NaN is no zero: u~ of a zero pair is cleared, so that
+        // the entries beside a non-finite one stay what they are)
+        const uint16_t u0 = (uint16_t)(d2h_via_f32(t.x) & keep), u1 = (uint16_t)(d2h_via_f32(t.y) & keep);
         if (w == (h & 3)) {
             uint16_t *cu = A.comp_u + ((size_t)tile * r + h) * D + 32 * j + i;
             cu[0] = u0;
