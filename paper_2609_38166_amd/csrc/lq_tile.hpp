@@ -508,11 +508,13 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
     }
 
     // ------------------------------------------------------------------ quantize
-    // y[b] = sum over this thread's key channels of M x, x by lane of the row
+    // y[b] = sum over this thread's key channels of M x, x by lane of the row.  (These
+    // sums and those over value channels start from +0: a product alone would make a
+    // sum of zeros -0, and with it the FP16 bits of a token and the sign of a residual.)
     auto keys_dot = [&](double x, double *y) {
         const double x0 = row_lane(x, 0);
 #pragma unroll
-        for (int b = 0; b < VPT; ++b) y[b] = M(0, b) * x0;
+        for (int b = 0; b < VPT; ++b) y[b] = fma(M(0, b), x0, 0.0);
 #pragma unroll
         for (int a = 1; a < 8; ++a) {
             const double xa = row_lane(x, a);
@@ -564,7 +566,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
             t.y *= f;
             share_pairs(sh, t, y, tid);
             x = sum_values(sh, [&](int a) {             // x_k = sum_v M_kv y_v
-                double s = M(a, 0) * y[0];
+                double s = fma(M(a, 0), y[0], 0.0);
 #pragma unroll
                 for (int b = 1; b < VPT; ++b) s = fma(M(a, b), y[b], s);
                 return s;

@@ -1,0 +1,52 @@
+"""The whole-tile kernels at the edges of arithmetic: zeros of either sign, decays that overflow FP16."""
+import numpy as np
+import pytest
+
+from paper_2609_38166_amd import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from oracle import oracle as O  # noqa: E402
+from paper_2609_38166_amd import binding as B  # noqa: E402
+from tests import gpu_harness as H  # noqa: E402
+
+
+def _random(n, seed):
+    """[n][key][value]"""
+    return np.random.default_rng(seed).standard_normal((n, 128, 128)).astype(np.float32).astype(np.float64)
+
+
+def _quantized(wl, S):
+    dims = H.gdims(wl)
+    st = B.State.empty(dims)
+    B.leapquant_quantize_state(dims, H.dev(S.transpose(0, 2, 1), torch.float32), st)
+    return dims, st
+
+
+@pytest.mark.parametrize("code", [synth.CODE_INT8, synth.CODE_E4M3])
+@pytest.mark.parametrize("kind", ["keys", "values", "sparse"])
+def test_a_zero_channel_has_positive_zero_tokens(kind, code):
+    """A sum of zeros of either sign is +0 (as the oracle's, which starts from 0): so are the token entries of a key
+    or value channel that holds only zeros, whatever the sign of the products that meet there."""
+    S = np.abs(_random(2, 4))
+    if kind == "keys":                  # a zero key channel of an all-negative state
+        S = -S
+        S[:, [5, 77]] = 0.0
+    elif kind == "values":              # a value channel of negative zeros under positive keys
+        S[:, :, [5, 77]] = -0.0
+    else:                               # most channels zero, their entries -0
+        rng = np.random.default_rng(5)
+        S = -(np.maximum(rng.standard_normal((2, 128, 1)), 0) * np.maximum(rng.standard_normal((2, 1, 128)), 0))
+        S = S.astype(np.float32).astype(np.float64)
+    wl = synth.Workload("zeros", 2, 1, 1, 0, 4, 1, synth.GATE_SCALAR, code=code)
+    rep = H.download_rep(_quantized(wl, S)[1])
+    want = [O.quantize(H.ocfg(wl), x) for x in S]
+    for f in ("Kt", "Ut"):
+        w = np.stack([getattr(x, f) for x in want])
+        assert int((H.f16_bits(rep[f]) != H.f16_bits(w)).sum()) == 0, f
+    if code == synth.CODE_E4M3:         # k~ >= 0 times +0 taken from a zero leaves it as it is
+        bits = np.where(np.signbit(S), 0x80, 0)
+        zero = np.broadcast_to((S == 0).all(axis=1, keepdims=True), S.shape)
+        assert zero.any() or kind == "keys"
+        assert int((rep["Z"][zero] != bits[zero]).sum()) == 0
