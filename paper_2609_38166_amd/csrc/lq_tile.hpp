@@ -413,9 +413,11 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
 #pragma unroll
                     for (int e = 0; e < 4; ++e) av[e] = (double)(h ? f[3 - e] : f[7 - e]);
                 }
+                // (an empty slot's key is 0 whatever the decay: 0 times an infinite one is a NaN)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    sh.key[w][s0 - e][c] = P * (double)h2f((uint16_t)(s0 - e < n ? rk[e] : 0u));
+                    const double key = P * (double)h2f((uint16_t)rk[e]);
+                    sh.key[w][s0 - e][c] = s0 - e < n ? key : 0.0;
                     P *= av[e];
                 }
                 // values: lane (record, 4-channel segment) of the wave's two records

@@ -50,3 +50,38 @@ def test_a_zero_channel_has_positive_zero_tokens(kind, code):
         zero = np.broadcast_to((S == 0).all(axis=1, keepdims=True), S.shape)
         assert zero.any() or kind == "keys"
         assert int((rep["Z"][zero] != bits[zero]).sum()) == 0
+
+
+# records per tile: oldest pass (and its last product of four) full or not
+P = np.array([3, 4, 8, 9, 10, 14, 17, 25])
+
+
+@pytest.mark.parametrize("gate", [synth.GATE_SCALAR, synth.GATE_DIAG])
+def test_an_infinite_decay_meets_no_empty_slot(gate):
+    """FP16 has no decay above 65504: a larger one is an infinity, which every older record and the base take over.
+    The slots of a pass that hold no record take no part in it (0 times an infinity would be a NaN)."""
+    n, W = len(P), 25
+    wl = synth.Workload("inf", n, 1, 1, 0, W, 0, gate)
+    cfg, dims, rng = H.ocfg(wl), H.gdims(wl), np.random.default_rng(8)
+    reps = [O.quantize(cfg, x) for x in rng.uniform(0.5, 1.0, (n, 128, 128))]       # every code is positive
+    st = B.State.empty(dims)
+    H.upload_rep(st, np.arange(n), *(np.stack([getattr(x, f) for x in reps]) for f in ("Z", "delta", "c", "Kt", "Ut")))
+    f16 = lambda x: x.astype(np.float16).astype(np.float64)      # noqa: E731
+    a = f16(rng.uniform(0.6, 1.0, (n, W, wl.g)))
+    k, u = f16(rng.uniform(0.5, 1.0, (n, W, 128))), f16(rng.uniform(0.5, 1.0, (n, W, 128)))
+    a[np.arange(n), P - 1, 0] = np.inf
+    H.upload_records(st, a, k, u)
+    st.rec_len.view(-1)[:] = torch.as_tensor(P, dtype=torch.int32, device="cuda")
+    out = torch.empty((n, 128, 128), dtype=torch.float32, device="cuda")
+    B.leapquant_dequantize_state(dims, st, out)
+    got = out.cpu().numpy().transpose(0, 2, 1)
+    for i, p in enumerate(P):
+        want = O.reconstruct(cfg, reps[i], None, a[i, :p], k[i, :p], u[i, :p])
+        hit = np.zeros(128, bool)
+        hit[:1 if gate else 128] = True                         # the key channels that the infinity decays
+        assert np.isinf(want[hit]).mean() == 1.0 and np.isfinite(want[~hit]).all()
+        assert np.isnan(got[i]).sum() == 0 and np.isinf(got[i][hit]).all(), p
+        if not gate:
+            continue
+        # one rounding to fp32 of sums in fp64
+        assert H.rel_rows(got[i][~hit].reshape(1, -1), want[~hit].reshape(1, -1)) < 6.1e-8
