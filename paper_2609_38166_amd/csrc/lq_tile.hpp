@@ -363,7 +363,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
 #pragma unroll
         for (int a = 0; a < 8; ++a)
 #pragma unroll
-            for (int b = 0; b < VPT; ++b) M(a, b) = 0.0;
+            for (int b = 0; b < VPT; ++b) M(a, b) = -0.0;      // (a sum of -0 stays -0)
 
         // decay of everything newer than the pass: key channel 32 w + (lane & 31)
         double carry = 1.0;
@@ -413,11 +413,12 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
 #pragma unroll
                     for (int e = 0; e < 4; ++e) av[e] = (double)(h ? f[3 - e] : f[7 - e]);
                 }
-                // (an empty slot's key is 0 whatever the decay: 0 times an infinite one is a NaN)
+                // (an empty slot's key is -0 whatever the decay: 0 times an infinite one is a
+                // NaN, and -0 times its value +0 adds nothing, to a sum of negative zeros neither)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const double key = P * (double)h2f((uint16_t)rk[e]);
-                    sh.key[w][s0 - e][c] = s0 - e < n ? key : 0.0;
+                    sh.key[w][s0 - e][c] = s0 - e < n ? key : -0.0;
                     P *= av[e];
                 }
                 // values: lane (record, 4-channel segment) of the wave's two records

@@ -85,3 +85,40 @@ def test_an_infinite_decay_meets_no_empty_slot(gate):
             continue
         # one rounding to fp32 of sums in fp64
         assert H.rel_rows(got[i][~hit].reshape(1, -1), want[~hit].reshape(1, -1)) < 6.1e-8
+
+
+@pytest.mark.parametrize("gate", [synth.GATE_SCALAR, synth.GATE_DIAG])
+@pytest.mark.parametrize("r,code", [(0, synth.CODE_BF16), (0, synth.CODE_E4M3), (3, synth.CODE_E4M3), (9, synth.CODE_E4M3)])
+def test_a_negative_zero_stays_one(r, code, gate):
+    """A sum of negative zeros is -0 in the export, and in the codes that have one (E4M3, BF16) after the commit."""
+    n, W = len(P), 25
+    wl = synth.Workload("mzero", n, 1, 1, 0, W, r, gate, code=code)
+    cfg, dims, rng = H.ocfg(wl), H.gdims(wl), np.random.default_rng(9 + r)
+    S = _random(n, 10)
+    minus = rng.random(S.shape) < 0.3
+    S[minus] = -0.0
+    reps = [O.quantize(H.ocfg(wl, n_comp=0), x) for x in S]
+    f16 = lambda x: x.astype(np.float16).astype(np.float64)      # noqa: E731
+    still = np.arange(0, 128, 2)                                 # value channels that nothing is added to
+    for x in reps:
+        x.Kt, x.Ut = f16(rng.uniform(0, 0.1, (r, 128))), f16(rng.standard_normal((r, 128)))
+        x.Ut[:, still] = -0.0
+    st = B.State.empty(dims)
+    H.upload_rep(st, np.arange(n), *(np.stack([getattr(x, f) for x in reps]) for f in ("Z", "delta", "c", "Kt", "Ut")))
+    a = f16(rng.uniform(0.6, 1.0, (n, W, wl.g)))
+    k, u = f16(rng.uniform(0, 0.1, (n, W, 128))), f16(rng.standard_normal((n, W, 128)))
+    u[:, :, still] = -0.0
+    H.upload_records(st, a, k, u)
+    for past in (np.zeros_like(P), P):
+        st.rec_len.view(-1)[:] = torch.as_tensor(past, dtype=torch.int32, device="cuda")
+        want = np.stack([O.reconstruct(cfg, reps[i], None, a[i, :p], k[i, :p], u[i, :p]) for i, p in enumerate(past)])
+        out = torch.empty((n, 128, 128), dtype=torch.float32, device="cuda")
+        B.leapquant_dequantize_state(dims, st, out)
+        got = out.cpu().numpy().transpose(0, 2, 1)
+        zero = want == 0
+        assert (zero & np.signbit(want) & minus).sum() > 1000 * n and np.array_equal(zero, got == 0)
+        assert int((np.signbit(got) != np.signbit(want))[zero].sum()) == 0
+    if r == 0:
+        B.leapquant_window_commit(dims, st)
+        rep = H.download_rep(st)
+        assert int((rep["Z"] != np.stack([O.quantize(cfg, x).Z for x in want])).sum()) == 0
