@@ -441,14 +441,23 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
 #pragma unroll
                     for (int e = 0; e < 4; ++e) av[e] = (double)(h ? f[3 - e] : f[7 - e]);
                 }
-                // (an empty slot's key is -0 whatever the decay: 0 times an infinite one is a
-                // NaN, and -0 times its value +0 adds nothing, to a sum of negative zeros neither)
+                double key[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const double key = P * (double)h2f((uint16_t)rk[e]);
-                    sh.key[w][s0 - e][c] = s0 - e < n ? key : -0.0;
+                    key[e] = P * (double)h2f((uint16_t)rk[e]);
                     P *= av[e];
                 }
+                // an empty slot's key is -0 whatever the decay: 0 times an infinite one is a
+                // NaN, and -0 times its value +0 adds nothing, to a sum of negative zeros neither
+                if (n < TCH) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        key[e] = s0 - e < n ? key[e] : -0.0;
+                        asm volatile("" : "+v"(key[e]));        // (stays in its branch)
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sh.key[w][s0 - e][c] = key[e];
                 // values: lane (record, 4-channel segment) of the wave's two records
                 const int s = 2 * w + h;
                 double *val = &sh.val[t & 1][s][4 * c];
