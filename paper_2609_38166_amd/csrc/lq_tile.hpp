@@ -323,8 +323,30 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
         asm volatile("" ::: "memory");              // (from here on the fit writes there)
     } else {
         const int p = p_given >= 0 ? p_given : A.rec_len[tile];
+        // the base's codes, row v's 16-byte chunk c at chunk (c + (v & 15)) mod SEGS of
+        // its row: the 16 rows that a read touches then spread over the banks
+        constexpr int SEGS = D * CodeFmt<CODE>::BITS / 8 / 16, NCP = CodeRows<CODE>::value * SEGS / TT;
+        auto copy_codes = [&](int v0, uint4 *to) {  // rows v0 .. v0 + CodeRows - 1
+            const uint4 *zt = (const uint4 *)(A.codes + ((size_t)tile * D + v0) * (SEGS * 16));
+#pragma unroll
+            for (int x = 0; x < NCP; ++x) {
+                const int P = TT * x + (int)threadIdx.x, v = P / SEGS, c = P % SEGS;
+                dma16(zt + v * SEGS + (c + 16 * SEGS - (v & 15)) % SEGS, lds_addr(to + TT * x + 64 * w));
+            }
+        };
+        auto copy_base = [&]() {
+            if constexpr (!IsBF16<CODE>::value) {
+                if (tid < 32) dma16(A.scale + tvec + 4 * tid, lds_addr(sh.scale));
+                if (w == 1 && (tid & 63) < 32) dma16(A.smooth + tvec + 4 * (tid & 63), lds_addr(sh.smooth));
+            }
+            copy_codes(0, sh.codes);
+        };
+        // (an export reads the base of every tile: it is on its way while rec_len is.  A
+        // commit leaves tiles alone, and starts with the records, which it needs first.)
+        if (MODE == TILE_DEQUANT) copy_base();
         if (p < 0 || p > A.window) {                                  // corrupt: tile untouched
             if (tid == 0) atomicOr(A.err, (int)LQ_DEVERR_BAD_REC_LEN);
+            if (MODE == TILE_DEQUANT) wait_vm_all();                  // (no copy outlives its LDS)
             return;
         }
         if (MODE == TILE_COMMIT) {
@@ -372,22 +394,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
             }
         };
         if (passes > 0) load_pass(0);
-        // the base's codes, row v's 16-byte chunk c at chunk (c + (v & 15)) mod SEGS of
-        // its row: the 16 rows that a read touches then spread over the banks
-        constexpr int SEGS = D * CodeFmt<CODE>::BITS / 8 / 16, NCP = CodeRows<CODE>::value * SEGS / TT;
-        if constexpr (!IsBF16<CODE>::value) {
-            if (tid < 32) dma16(A.scale + tvec + 4 * tid, lds_addr(sh.scale));
-            if (w == 1 && (tid & 63) < 32) dma16(A.smooth + tvec + 4 * (tid & 63), lds_addr(sh.smooth));
-        }
-        auto copy_codes = [&](int v0, uint4 *to) {  // rows v0 .. v0 + CodeRows - 1
-            const uint4 *zt = (const uint4 *)(A.codes + ((size_t)tile * D + v0) * (SEGS * 16));
-#pragma unroll
-            for (int x = 0; x < NCP; ++x) {
-                const int P = TT * x + (int)threadIdx.x, v = P / SEGS, c = P % SEGS;
-                dma16(zt + v * SEGS + (c + 16 * SEGS - (v & 15)) % SEGS, lds_addr(to + TT * x + 64 * w));
-            }
-        };
-        copy_codes(0, sh.codes);
+        if (MODE == TILE_COMMIT) copy_base();
 #pragma unroll
         for (int a = 0; a < 8; ++a)
 #pragma unroll
@@ -401,7 +408,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
             int lo, n;
             bounds(t, lo, n);
             const bool rec = t < nrp;
-            if (t == 0) wait_vm<NCP>();             // the first pass has landed (the codes may follow)
+            if (MODE == TILE_COMMIT && t == 0) wait_vm<NCP>();    // the first pass has landed (the codes may follow)
             else wait_vm_all();
             {
                 // keys: lane (c, h) folds the decay into slots 7 - 4 h - e, e = 0..3, newest first
@@ -506,30 +513,42 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
                 const uint32_t y = CodeFmt<CODE>::BITS * kb + 2 * e;
                 zoff[e] = 16 * ((y / 16 + i) % SEGS) + (y & 15);
             }
+            // (each row's codes are read from LDS one row ahead)
+            typedef typename Codes8<CODE>::type C8;
+            auto read_codes = [&](int b) -> C8 {
+                const uint4 *zv = 16 * b < CodeRows<CODE>::value ? sh.codes : (const uint4 *)sh.val;
+                const uint8_t *zr = (const uint8_t *)&zv[((16 * b + i) & (CodeRows<CODE>::value - 1)) * SEGS];
+                if constexpr (CODE <= 1) {
+                    return *(const uint2 *)(zr + zoff[0]);
+                } else if constexpr (CODE == 2) {
+                    return make_uint2(*(const uint32_t *)(zr + zoff[0]), 0u);
+                } else if constexpr (CODE == 3) {
+                    return make_uint2(*(const uint16_t *)(zr + zoff[0]) | ((uint32_t) * (const uint16_t *)(zr + zoff[1]) << 16),
+                                      *(const uint16_t *)(zr + zoff[2]));
+                } else {
+                    return *(const uint4 *)(zr + zoff[0]);
+                }
+            };
+            C8 z = read_codes(0);
+            float dl = IsBF16<CODE>::value ? 1.0f : sh.scale[i];
 #pragma unroll
             for (int b = 0; b < VPT; ++b) {
-                const int v = 16 * b + i;
-                typename Codes8<CODE>::type z;
-                if (16 * b == CodeRows<CODE>::value) {
-                    wait_vm_all();
-                    __syncthreads();
+                C8 zn = z;
+                float dn = dl;
+                if (b + 1 < VPT) {
+                    if (16 * (b + 1) == CodeRows<CODE>::value) {
+                        wait_vm_all();
+                        __syncthreads();
+                    }
+                    zn = read_codes(b + 1);
+                    if (!IsBF16<CODE>::value) dn = sh.scale[16 * (b + 1) + i];
                 }
-                const uint4 *zv = 16 * b < CodeRows<CODE>::value ? sh.codes : (const uint4 *)sh.val;
-                const uint8_t *zr = (const uint8_t *)&zv[(v & (CodeRows<CODE>::value - 1)) * SEGS];
-                if constexpr (CODE <= 1) {
-                    z = *(const uint2 *)(zr + zoff[0]);
-                } else if constexpr (CODE == 2) {
-                    z = make_uint2(*(const uint32_t *)(zr + zoff[0]), 0u);
-                } else if constexpr (CODE == 3) {
-                    z = make_uint2(*(const uint16_t *)(zr + zoff[0]) | ((uint32_t) * (const uint16_t *)(zr + zoff[1]) << 16),
-                                   *(const uint16_t *)(zr + zoff[2]));
-                } else {
-                    z = *(const uint4 *)(zr + zoff[0]);
-                }
-                const double dv = IsBF16<CODE>::value ? 1.0 : (double)sh.scale[v];
+                const double dv = IsBF16<CODE>::value ? 1.0 : (double)dl;
 #pragma unroll
                 for (int a = 0; a < 8; ++a) M(a, b) = fma(cv[a], code8_value<CODE>(z, a) * dv, M(a, b));
-                __builtin_amdgcn_sched_barrier(0);      // one row's codes live at a time beside the block
+                __builtin_amdgcn_sched_barrier(0);      // two rows' codes live at a time beside the block
+                z = zn;
+                dl = dn;
             }
         }
 
