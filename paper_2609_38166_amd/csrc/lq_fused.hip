@@ -25,13 +25,11 @@ namespace {
 template <int CODE>
 union FusedShared {
     DecodeShared<CODE> d;
-    TileShared t;
+    TileShared<CODE> t;
 };
 
-template <int CODE> struct FusedOcc { static constexpr int value = IsBF16<CODE>::value ? 2 : 3; };
-
 template <int GATE, int CODE, int RULE>
-__global__ __launch_bounds__(NT, FusedOcc<CODE>::value) void decode_commit_kernel(DecodeArgs a, TileArgs c) {
+__global__ __launch_bounds__(NT, TileOcc<CODE>::value) void decode_commit_kernel(DecodeArgs a, TileArgs c) {
     __shared__ FusedShared<CODE> sh;
     const int tile = blockIdx.x;
     const int n = decode_body<GATE, CODE, RULE>(a, sh.d, tile);

@@ -7,8 +7,8 @@ namespace lq {
 namespace {
 
 template <int GATE, int CODE, int MODE>
-__global__ __launch_bounds__(TT, 3) void tile_kernel(TileArgs A) {
-    __shared__ TileShared sh;
+__global__ __launch_bounds__(TT, TileOcc<CODE>::value) void tile_kernel(TileArgs A) {
+    __shared__ TileShared<CODE> sh;
     tile_body<GATE, CODE, MODE>(A, sh, blockIdx.x, -1);
 }
 

@@ -134,10 +134,11 @@ struct TileArgs {
     int smooth_on;
 };
 
-// Value channels whose codes the reconstruction copies into LDS when it starts:
-// all, or the first half of the BF16 state's 32 KiB.
-template <int CODE> struct CodeRows { static constexpr int value = IsBF16<CODE>::value ? D / 2 : D; };
+// Workgroups per CU: three (166 VGPRs, 47 KiB of LDS).  The BF16 state's 32 KiB of codes
+// lie in LDS as a whole, so two.
+template <int CODE> struct TileOcc { static constexpr int value = IsBF16<CODE>::value ? 2 : 3; };
 
+template <int CODE>
 struct TileShared {
     union {
         struct {                            // reconstruction
@@ -145,7 +146,7 @@ struct TileShared {
             double val[2][TCH][D];          // record values, two passes in turn
             uint4 raw_ka[NW][64];           // copied records: a wave's keys, then decays
             uint4 raw_u[NW][32];            // two records' values of each wave
-            uint4 codes[D * D / 16];        // rows rotated by v & 15 chunks
+            uint4 codes[D * D * CodeFmt<CODE>::BITS / 128];    // rows rotated by v & 15 chunks
             float scale[D];
             float smooth[D];
         };
@@ -176,7 +177,8 @@ __device__ __forceinline__ constexpr int TURN_BLOCK(int q, int c) { return 8 * q
 // 4 waves through LDS.  One barrier; `buf` alternates between calls, so a
 // call's writes meet only reads that the previous call's barrier has ended.
 // Lane (row j, i) receives channels 32 j + i and 32 j + 16 + i (b = 2 j, 2 j + 1).
-__device__ __forceinline__ double2 sum_keys(TileShared &sh, const double *v, int buf, int tid) {
+template <typename Shared>
+__device__ __forceinline__ double2 sum_keys(Shared &sh, const double *v, int buf, int tid) {
     const int lane = tid & 63, w = tid >> 6;
     double s0, s1;
     rows4_reduce_scatter(v, s0, s1);
@@ -190,7 +192,8 @@ __device__ __forceinline__ double2 sum_keys(TileShared &sh, const double *v, int
 
 // The lane's pair of a value vector to every lane of the wave: v[b] = channel
 // 16 b + i (through the wave's own LDS copy; no barrier).
-__device__ __forceinline__ void share_pairs(TileShared &sh, double2 t, double *v, int tid) {
+template <typename Shared>
+__device__ __forceinline__ void share_pairs(Shared &sh, double2 t, double *v, int tid) {
     const int lane = tid & 63, w = tid >> 6, i = lane & 15;
     __builtin_amdgcn_wave_barrier();
     *(double2 *)&sh.vec[w][2 * lane] = t;
@@ -212,8 +215,8 @@ __device__ __forceinline__ void share_pairs(TileShared &sh, double2 t, double *v
 // partial is stored as soon as it is made, so that the stores run beside the
 // next one's arithmetic (4% off a commit and 6% off a quantization against
 // storing the eight together).
-template <typename F>
-__device__ __forceinline__ double sum_values(TileShared &sh, F part, int tid) {
+template <typename Shared, typename F>
+__device__ __forceinline__ double sum_values(Shared &sh, F part, int tid) {
     const int i = tid & 15, c = i & 7, h = i >> 3;
     double *r = sh.red[tid >> 4];
     __builtin_amdgcn_wave_barrier();
@@ -259,7 +262,8 @@ __device__ __forceinline__ double wave_sum_half(double z) {
     return a + b;
 }
 
-__device__ __forceinline__ double sum_nrm(const TileShared &sh, int buf) {
+template <typename Shared>
+__device__ __forceinline__ double sum_nrm(const Shared &sh, int buf) {
     return (sh.nrm[buf][0] + sh.nrm[buf][1]) + (sh.nrm[buf][2] + sh.nrm[buf][3]);
 }
 
@@ -271,7 +275,7 @@ __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" :
 // without the request mask: the decode step fused with the commit passes the
 // count it has just made.
 template <int GATE, int CODE, int MODE>
-__device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int tile, int p_given) {
+__device__ __forceinline__ void tile_body(const TileArgs &A, TileShared<CODE> &sh, int tile, int p_given) {
     // lane coordinates: value block i, row j of the wave, wave w; re-derived from
     // an opaque thread index at phase boundaries, so that the compiler recomputes
     // the addresses built from them instead of holding them across phases
@@ -309,7 +313,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
 #pragma unroll
         for (int x = 0; x < 2 * VPT; ++x) in[x] = *(const v4f *)(S + (size_t)(8 * x) * D);
         v4f *turn = (v4f *)sh.red[4 * w];           // (LDS that is this wave's in the fit too: no barrier ends it)
-        static_assert(sizeof(sh.red) / NW >= 16 * 128 && offsetof(TileShared, red) % 16 == 0 && sizeof(sh.red[0]) % 4 == 0);
+        static_assert(sizeof(sh.red) / NW >= 16 * 128 && offsetof(TileShared<CODE>, red) % 16 == 0 && sizeof(sh.red[0]) % 4 == 0);
 #pragma unroll
         for (int b = 0; b < VPT; ++b) {
             turn[TURN_ROWS(lane)] = in[2 * b];
@@ -325,21 +329,18 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
         const int p = p_given >= 0 ? p_given : A.rec_len[tile];
         // the base's codes, row v's 16-byte chunk c at chunk (c + (v & 15)) mod SEGS of
         // its row: the 16 rows that a read touches then spread over the banks
-        constexpr int SEGS = D * CodeFmt<CODE>::BITS / 8 / 16, NCP = CodeRows<CODE>::value * SEGS / TT;
-        auto copy_codes = [&](int v0, uint4 *to) {  // rows v0 .. v0 + CodeRows - 1
-            const uint4 *zt = (const uint4 *)(A.codes + ((size_t)tile * D + v0) * (SEGS * 16));
-#pragma unroll
-            for (int x = 0; x < NCP; ++x) {
-                const int P = TT * x + (int)threadIdx.x, v = P / SEGS, c = P % SEGS;
-                dma16(zt + v * SEGS + (c + 16 * SEGS - (v & 15)) % SEGS, lds_addr(to + TT * x + 64 * w));
-            }
-        };
+        constexpr int SEGS = D * CodeFmt<CODE>::BITS / 8 / 16, NCP = D * SEGS / TT;
         auto copy_base = [&]() {
             if constexpr (!IsBF16<CODE>::value) {
                 if (tid < 32) dma16(A.scale + tvec + 4 * tid, lds_addr(sh.scale));
                 if (w == 1 && (tid & 63) < 32) dma16(A.smooth + tvec + 4 * (tid & 63), lds_addr(sh.smooth));
             }
-            copy_codes(0, sh.codes);
+            const uint4 *zt = (const uint4 *)(A.codes + (size_t)tile * D * (SEGS * 16));
+#pragma unroll
+            for (int x = 0; x < NCP; ++x) {
+                const int P = TT * x + (int)threadIdx.x, v = P / SEGS, c = P % SEGS;
+                dma16(zt + v * SEGS + (c + 16 * SEGS - (v & 15)) % SEGS, lds_addr(sh.codes + TT * x + 64 * w));
+            }
         };
         // (an export reads the base of every tile: it is on its way while rec_len is.  A
         // commit leaves tiles alone, and starts with the records, which it needs first.)
@@ -503,9 +504,6 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
 #pragma unroll
             for (int a = 0; a < 8; ++a)
                 cv[a] = sh.key[w][0][8 * j + a] * (IsBF16<CODE>::value ? 1.0 : (double)sh.smooth[8 * kb + a]);
-            // (the record values are no longer read: the BF16 state's second half lands there
-            // beside the first half's arithmetic)
-            if constexpr (IsBF16<CODE>::value) copy_codes(D / 2, (uint4 *)sh.val);
             // where the 8 codes lie in a row (the 6-bit ones may cross a chunk)
             uint32_t zoff[CODE == 3 ? 3 : 1];
 #pragma unroll
@@ -516,8 +514,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
             // (each row's codes are read from LDS one row ahead)
             typedef typename Codes8<CODE>::type C8;
             auto read_codes = [&](int b) -> C8 {
-                const uint4 *zv = 16 * b < CodeRows<CODE>::value ? sh.codes : (const uint4 *)sh.val;
-                const uint8_t *zr = (const uint8_t *)&zv[((16 * b + i) & (CodeRows<CODE>::value - 1)) * SEGS];
+                const uint8_t *zr = (const uint8_t *)&sh.codes[(16 * b + i) * SEGS];
                 if constexpr (CODE <= 1) {
                     return *(const uint2 *)(zr + zoff[0]);
                 } else if constexpr (CODE == 2) {
@@ -536,10 +533,6 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
                 C8 zn = z;
                 float dn = dl;
                 if (b + 1 < VPT) {
-                    if (16 * (b + 1) == CodeRows<CODE>::value) {
-                        wait_vm_all();
-                        __syncthreads();
-                    }
                     zn = read_codes(b + 1);
                     if (!IsBF16<CODE>::value) dn = sh.scale[16 * (b + 1) + i];
                 }
@@ -683,14 +676,21 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared &sh, int
     if constexpr (IsBF16<CODE>::value) {
         // BF16 state: every entry rounded to nearest even through fp32 (the
         // window-end rounding of the per-window BF16 variant), unit scales
-        constexpr int ROW = D * 2;
+        const int lane = tid & 63;
+        uint4 *turn = (uint4 *)sh.key[w];
+        uint8_t *to = A.codes + ((size_t)tile * D + (lane >> 2)) * (2 * D) + 64 * w + 16 * (lane & 3);
 #pragma unroll
         for (int b = 0; b < VPT; ++b) {
             uint32_t o[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 o[e] = (uint32_t)f2bf((float)M(2 * e, b)) | ((uint32_t)f2bf((float)M(2 * e + 1, b)) << 16);
-            *(uint4 *)(A.codes + ((size_t)tile * D + 16 * b + i) * ROW + 16 * kb) = make_uint4(o[0], o[1], o[2], o[3]);
+            // (a wave's part of a row is 64 bytes: turned in LDS, a store covers 16 of them)
+            turn[64 * (b & 1) + 4 * i + (j ^ ((i >> 1) & 3))] = make_uint4(o[0], o[1], o[2], o[3]);
+            __builtin_amdgcn_wave_barrier();
+            const uint4 z = turn[64 * (b & 1) + (lane & 60) + ((lane & 3) ^ ((lane >> 3) & 3))];
+            __builtin_amdgcn_wave_barrier();
+            *(uint4 *)(to + (size_t)(16 * b) * (2 * D)) = z;
         }
         if (tid < D) {
             A.smooth[tvec + tid] = 1.0f;
