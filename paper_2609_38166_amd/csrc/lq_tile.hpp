@@ -292,6 +292,29 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared<CODE> &s
     const size_t tvec = (size_t)tile * D;
     const int r = A.n_comp;
 
+    if constexpr (IsBF16<CODE>::value && MODE == TILE_QUANTIZE) {
+        // the BF16 state has no tokens, scales or smoothing: every entry rounded where it is
+        // (through the block and its turns one state took 4.18 us, this 2.46; 2048 states 37.3 and 34.5)
+        const v4f *S = (const v4f *)(A.S_in + (size_t)tile * D * D) + 2 * tid;
+        uint4 *to = (uint4 *)(A.codes + (size_t)tile * D * D * 2) + tid;
+        constexpr int N = D * D / 8 / TT;
+        v4f in[2 * N];
+#pragma unroll
+        for (int x = 0; x < 2 * N; ++x) in[x] = S[2 * TT * (x >> 1) + (x & 1)];
+#pragma unroll
+        for (int x = 0; x < N; ++x) {
+            const v4f a = in[2 * x], b = in[2 * x + 1];
+            to[TT * x] = make_uint4(f2bf(a.x) | ((uint32_t)f2bf(a.y) << 16), f2bf(a.z) | ((uint32_t)f2bf(a.w) << 16),
+                                    f2bf(b.x) | ((uint32_t)f2bf(b.y) << 16), f2bf(b.z) | ((uint32_t)f2bf(b.w) << 16));
+        }
+        if (tid < D) {
+            A.smooth[tvec + tid] = 1.0f;
+            A.scale[tvec + tid] = 1.0f;
+        }
+        if (tid == 0) A.rec_len[tile] = 0;
+        return;
+    }
+
     // the block: M(a, b) = M[8 kb + a][16 b + i], in the accumulator layout of
     // v_mfma_f64_16x16x4 (accumulator (a >> 2, b): row j + 4 (a & 3), column i)
     v4d m4[2][VPT];
