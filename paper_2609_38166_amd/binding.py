@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from dataclasses import dataclass
 
 import torch
@@ -54,11 +55,38 @@ class lq_state(C.Structure):
 
 
 _L = None
-# the native marshalling of regular calls (py_csrc/marshal.cpp) and the addresses
-# of the entry points it calls
+# the native marshalling of regular calls (py_csrc/marshal.cpp; once the library is
+# loaded, it or what stands in for it) and the addresses of the entry points it calls
 _M = None
 _FN = {"leapquant_decode_step": 0, "leapquant_decode_step_general": 0, "leapquant_decode_step_commit": 0,
        "leapquant_window_commit": 0}
+
+
+class _NoMarshal:
+    """Stands in for the native marshalling where it cannot be loaded: every call is
+    left to the Python checks (about 17 us a call, the same results)."""
+
+    @staticmethod
+    def step(*args):
+        return None
+
+    step_general = commit = step
+
+
+def _load_marshal(addr):
+    """The native marshalling, set up, or its stand-in: the extension is tied to one
+    build of torch and takes no call that the Python path does not."""
+    try:
+        from . import _marshal as native
+        built = getattr(native, "torch_version", None)
+        if built != torch.__version__:
+            raise ImportError(f"_marshal.so was built against torch {built}, this is {torch.__version__}")
+    except ImportError as e:
+        warnings.warn(f"calls are checked and unpacked in Python, about 17 us each ({e}); "
+                      "paper_2609_38166_amd/build.py builds _marshal.so", RuntimeWarning, stacklevel=3)
+        return _NoMarshal
+    native.setup(lq_dims, State, FIELDS, addr["leapquant_state_bytes"])
+    return native
 
 
 def _lib():
@@ -86,15 +114,10 @@ def _lib():
         for n in EXPORTS:
             if n not in ("leapquant_strerror", "leapquant_last_hip_error"):
                 getattr(L, n).restype = C.c_int32
-        marshal_path = os.path.join(_PKG, "_marshal.so")
-        if not os.path.exists(marshal_path):
-            raise ImportError(f"{marshal_path} is missing: build it with paper_2609_38166_amd/build.py")
-        from . import _marshal
         addr = {n: C.cast(getattr(L, n), vp).value for n in EXPORTS}
-        _marshal.setup(lq_dims, State, FIELDS, addr["leapquant_state_bytes"])
         for n in _FN:
             _FN[n] = addr[n]
-        _M, _L = _marshal, L
+        _M, _L = _load_marshal(addr), L
     return _L
 
 

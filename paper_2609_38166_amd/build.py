@@ -12,6 +12,7 @@ import os
 import subprocess
 import sys
 import tempfile
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -22,6 +23,7 @@ BENCH_LIB = os.path.join(PKG, "libleapquant_bench.so")
 # argument marshalling of the Python binding (host code, against torch's headers)
 MARSHAL_LIB = os.path.join(PKG, "_marshal.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CXX = "g++"
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -73,6 +75,17 @@ def _compile(srcs, out, verbose, defines=()):
 
 
 def _compile_marshal(verbose):
+    """The extension saves the binding host time and is tied to this torch's headers;
+    where it cannot be built, none is left and the binding does without it."""
+    try:
+        _build_marshal(verbose)
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        if os.path.exists(MARSHAL_LIB):
+            os.remove(MARSHAL_LIB)
+        warnings.warn(f"_marshal.so is not built, the binding will check calls in Python: {e}", RuntimeWarning)
+
+
+def _build_marshal(verbose):
     import sysconfig
 
     import torch
@@ -80,7 +93,8 @@ def _compile_marshal(verbose):
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     inc = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"], "/opt/rocm/include", *include_paths()]
     tmp = MARSHAL_LIB + ".tmp"
-    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
+    cmd = [CXX, "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
+           f'-DLQ_TORCH_VERSION="{torch.__version__}"',
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(x for d in inc for x in ("-isystem", d)),
            os.path.join(PKG, "py_csrc", "marshal.cpp"), "-o", tmp,
            "-L", lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]

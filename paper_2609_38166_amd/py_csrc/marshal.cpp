@@ -189,4 +189,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal(void) { return PyModule_Create(&module); }
+// (the binding uses the extension with the torch that it was built against only)
+PyMODINIT_FUNC PyInit__marshal(void) {
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", LQ_TORCH_VERSION) != 0) Py_CLEAR(m);
+    return m;
+}
