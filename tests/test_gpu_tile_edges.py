@@ -122,3 +122,29 @@ def test_a_negative_zero_stays_one(r, code, gate):
         B.leapquant_window_commit(dims, st)
         rep = H.download_rep(st)
         assert int((rep["Z"] != np.stack([O.quantize(cfg, x).Z for x in want])).sum()) == 0
+
+
+@pytest.mark.parametrize("sweeps", [1, 4, 64])
+@pytest.mark.parametrize("scale", [1e-38, 1e-20, 1e-6, 1e3, 1e20, 1e36])
+def test_the_sweeps_stay_in_range_at_extreme_magnitudes(scale, sweeps):
+    """Sweeps are scaled by one power of two per token, taken from the largest row norm: the direction (and with it
+    every token's key half) is the oracle's, which normalises every sweep, from fp32's smallest states to its largest."""
+    S = _random(3, 12)
+    S[1] *= 10.0 ** np.random.default_rng(13).uniform(-2, 0, (128, 1))     # rows of unlike size
+    S[2] = S[2, :, :1] * S[2, :1, :]                                       # one direction, then rounding only
+    S = (S * scale).astype(np.float32).astype(np.float64)
+    # (a value half beyond FP16 is infinite, and what it is taken from no state: one token then)
+    r = 1 if scale > 1e4 else 3
+    wl = synth.Workload("extreme", 3, 1, 1, 0, 4, r, synth.GATE_SCALAR)
+    cfg = H.ocfg(wl, power_iters=sweeps)
+    dims = H.gdims(wl, power_iters=sweeps)
+    st = B.State.empty(dims)
+    B.leapquant_quantize_state(dims, H.dev(S.transpose(0, 2, 1), torch.float32), st)
+    rep = H.download_rep(st)
+    for i, x in enumerate(S):
+        want = O.quantize(cfg, x)
+        n = 1 if i == 2 else r               # past the one direction the oracle fits the rounding of its own sums
+        assert np.abs(want.Kt[:n]).max() > 0
+        for f in ("Kt", "Ut"):
+            with np.errstate(over="ignore"):
+                assert int((H.f16_bits(rep[f][i][:n]) != H.f16_bits(getattr(want, f)[:n])).sum()) == 0, (i, f)
