@@ -64,7 +64,7 @@ _FN = {"leapquant_decode_step": 0, "leapquant_decode_step_general": 0, "leapquan
 
 class _NoMarshal:
     """Stands in for the native marshalling where it cannot be loaded: every call is
-    left to the Python checks (about 17 us a call, the same results)."""
+    left to the Python checks (about 16 us a call, the same results)."""
 
     @staticmethod
     def step(*args):
@@ -82,7 +82,7 @@ def _load_marshal(addr):
         if built != torch.__version__:
             raise ImportError(f"_marshal.so was built against torch {built}, this is {torch.__version__}")
     except ImportError as e:
-        warnings.warn(f"calls are checked and unpacked in Python, about 17 us each ({e}); "
+        warnings.warn(f"calls are checked and unpacked in Python, about 16 us each ({e}); "
                       "paper_2609_38166_amd/build.py builds _marshal.so", RuntimeWarning, stacklevel=3)
         return _NoMarshal
     native.setup(lq_dims, State, FIELDS, addr["leapquant_state_bytes"])

@@ -36,8 +36,9 @@ FLAGS = [
 # measured against the default on the KDA workload (8192 tiles, W = 64, r = 8):
 #  - decode: the max-ILP strategy, 1.7% less time per launch over the window
 #    positions (2.2% on the GQA GDN layer), no spill;
-#  - tile kernel (quantize, commit): the AMDGPU register-pressure trackers,
-#    6% less time per commit (quantize within 2%).
+#  - tile kernel: the AMDGPU register-pressure trackers, for the scalar gate's
+#    exports, which spill without them: 8192 E4M3 states with 33 records 291 us
+#    instead of 255 (2048: 76 and 73); commits and quantizations within 1%.
 SCHED = {
     "lq_decode.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
     "lq_tile.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers"],

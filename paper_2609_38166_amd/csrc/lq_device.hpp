@@ -33,22 +33,6 @@ __device__ __forceinline__ float row16_sum(float x) {
     return x;
 }
 
-// Sum over an aligned group of 8 lanes; every lane of the group receives it.
-__device__ __forceinline__ float row8_sum(float x) {
-    x += dpp<DPP_XOR1>(x);
-    x += dpp<DPP_XOR2>(x);
-    x += dpp<DPP_HALF_MIRROR>(x);
-    return x;
-}
-
-__device__ __forceinline__ float row16_max(float x) {
-    x = fmaxf(x, dpp<DPP_XOR1>(x));
-    x = fmaxf(x, dpp<DPP_XOR2>(x));
-    x = fmaxf(x, dpp<DPP_ROR4>(x));
-    x = fmaxf(x, dpp<DPP_ROR8>(x));
-    return x;
-}
-
 // (every lane of the row has a source under these controls, so the moves need
 // no old value: no register is cleared ahead of them)
 template <int CTRL>
@@ -63,13 +47,6 @@ __device__ __forceinline__ double row16_sum(double x) {
     x += dpp<DPP_XOR2>(x);
     x += dpp<DPP_ROR4>(x);
     x += dpp<DPP_ROR8>(x);
-    return x;
-}
-
-__device__ __forceinline__ double wave_sum(double x) {
-    x = row16_sum(x);
-    x += __shfl_xor(x, 16);
-    x += __shfl_xor(x, 32);
     return x;
 }
 
@@ -176,7 +153,6 @@ __device__ __forceinline__ float h2f(uint16_t h) {
 __device__ __forceinline__ uint16_t f2h(float f) {      // round to nearest even
     return __builtin_bit_cast(uint16_t, (_Float16)f);
 }
-__device__ __forceinline__ float f16_round(float f) { return h2f(f2h(f)); }
 
 // fp16 of the fp32 product a * b: two roundings as written.  Without the empty
 // asm the compiler emits one mixed-precision multiply (v_fma_mixlo_f16) that
@@ -212,11 +188,6 @@ __device__ __forceinline__ void unpack_h8(const uint4 &p, float *f) {
         f[2 * i] = h2f((uint16_t)(w[i] & 0xFFFFu));
         f[2 * i + 1] = h2f((uint16_t)(w[i] >> 16));
     }
-}
-
-// Byte `n` of a word as a signed int8 value, converted to fp32.
-__device__ __forceinline__ float s8_to_f(uint32_t w, int n) {
-    return (float)(int32_t)(int8_t)(uint8_t)(w >> (8 * n));
 }
 
 // OCP E4M3FN byte to fp32 (gfx950 converts the OCP format in hardware).
@@ -271,24 +242,6 @@ __device__ __forceinline__ float code_at(const uint32_t *w, int j) {
     return (float)sfield(span, 0, 6);
 }
 
-// 16 consecutive codes (the first 4 * BITS / 8 words of p) to fp32.
-template <int CODE>
-__device__ __forceinline__ void decode16(const uint4 &p, float *f) {
-    const uint32_t w[4] = {p.x, p.y, p.z, p.w};
-    if (CODE == 0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            f[4 * i + 0] = s8_to_f(w[i], 0);
-            f[4 * i + 1] = s8_to_f(w[i], 1);
-            f[4 * i + 2] = s8_to_f(w[i], 2);
-            f[4 * i + 3] = s8_to_f(w[i], 3);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) f[j] = code_at<CODE>(w, j);
-    }
-}
-
 // Pack 8 codes (integers, or E4M3 bytes) into the words of their format.
 template <int CODE>
 __device__ __forceinline__ uint2 encode8(const uint32_t *c) {
@@ -307,10 +260,6 @@ __device__ __forceinline__ uint2 encode8(const uint32_t *c) {
     for (int a = 0; a < 8; ++a) v |= (uint64_t)(c[a] & 0x3Fu) << (6 * a);
     return make_uint2((uint32_t)v, (uint32_t)(v >> 32));
 }
-
-// Non-temporal-free plain vector loads/stores through the vector memory path.
-template <typename T>
-__device__ __forceinline__ T ld(const T *p) { return *p; }
 
 // LDS byte address of a __shared__ object.
 __device__ __forceinline__ uint32_t lds_addr(const void *p) {

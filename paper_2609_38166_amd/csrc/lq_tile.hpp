@@ -2,35 +2,39 @@
 // their launches and by the decode step fused with the commit.
 // Whole-tile kernels: quantize a given state, commit a window, dequantize.
 //
-// One 256-thread workgroup (4 waves) owns one 128 x 128 tile held in
-// registers: wave w owns key channels 32 w .. 32 w + 31, and lane (row j, i) of
-// it the 8 x 8 block M[32 w + 8 j + a][16 b + i] of the state in paper
-// orientation (row = key channel): a memory instruction of a wave then touches
-// 16 neighbouring rows, not 16 rows 4 KiB apart, which met in few L2 channels.  A sum over value channels stays inside a
-// 16-lane row; a sum over key channels crosses the wave's rows in registers and
-// the waves through LDS: one barrier per power sweep.  A vector over key
-// channels never leaves its wave.  Three workgroups share a CU (166 VGPRs per
-// lane, 47 KiB of LDS each): the 128 registers of the fp64 block leave 40 for
-// everything else, so the code below keeps few values live across phases (lane
-// coordinates re-derived where used, the next pass's records copied straight
-// into LDS).
+// One 256-thread workgroup (4 waves) owns one 128 x 128 tile held in registers: wave w
+// owns key channels 32 w .. 32 w + 31, and lane (row j, i) of it the 8 x 8 block
+// M[32 w + 8 j + a][16 b + i] of the state in paper orientation (row = key channel).  A
+// sum over value channels stays inside a 16-lane row; a sum over key channels crosses
+// the wave's rows in registers and the waves through LDS: one barrier per power sweep.  A
+// vector over key channels never leaves its wave.  Three workgroups share a CU (168 VGPRs
+// per lane, 47 KiB of LDS each; two with the BF16 state): the 128 registers of the fp64
+// block leave 40 for everything else, so the code below keeps few values live across
+// phases (lane coordinates re-derived where used, the next pass's records copied
+// straight into LDS).
 //
-// What bounds it: fp64 issue, and in the sweeps the LDS transposes and the
-// barrier beside it.  A sweep is 128 FMA per lane (0.27 us per tile and CU at the
-// 2.05 GHz that the card holds under them); it takes 0.38 us with three
-// workgroups per CU and 0.70 us with one.  Measured at r = 8, 4 sweeps against
-// the layout before (a thread's block in a row of key blocks, two barriers and
-// five LDS round trips a sweep): quantize 48.6 -> 37.3 us for 32 tiles, 1543 ->
-// 1374 us for 16384; commit of 64 records (per-channel gate) 75.6 -> 55.3 us
-// for 32 tiles, 182 -> 150 us for 1024, 1245 -> 1060 us for 8192.
+// Memory.  The block's 16 neighbouring lanes hold 16 value rows, and an instruction that
+// loaded or stored as they hold it would touch 64 pieces of lines; states (and the BF16
+// state's codes) are therefore turned in LDS, each wave its own part, and move in whole
+// lines.  Codes of 8 bits and less are stored as held, 8 bytes a lane: turning them too
+// costs more than it gives where memory is the bound (quantize of 8192 states without
+// tokens 123 -> 129 us).
 //
-// The rank-one terms of the reconstruction (records, Compensator Tokens) go
-// through the fp64 matrix cores, v_mfma_f64_16x16x4: the same rate per cycle as
-// the vector unit's FMA, but one instruction per 16, two LDS reads per 16 x 16
-// product instead of four per 64 FMA, and less power: 77 TFLOP/s at 2.38 GHz
-// against 67 at 2.2 in a loop of nothing else.  Its accumulators are the 8 x 8
-// blocks (the operand rows are permuted to make them so).  Reconstruction and
-// fp32 store of 8192 tiles with 64 records and 8 tokens: 490 -> 425 us.
+// What bounds it: fp64 issue, and in the sweeps the LDS transposes and the barrier
+// beside it.  A sweep is 128 FMA per lane (0.25 us per tile and CU at the 2.07 GHz that
+// the card holds under them); it takes 0.41 us with three workgroups per CU (quantize of
+// 2048 states, 5 sweeps against 4) and 0.68 us with one (32 states).  Measured at r = 8, 4
+// sweeps against a layout with a thread's block in a row of key blocks, two barriers and
+// five LDS round trips a sweep: quantize 49.1 -> 36.9 us for 32 tiles, 212 -> 181 us for
+// 2048; commit of 64 records (per-channel gate) 72.3 -> 51.7 us for 32 tiles, 320 -> 269 us
+// for 2048, 1192 -> 1000 us for 8192 (out of cache).
+//
+// The rank-one terms of the reconstruction (records, Compensator Tokens) go through the
+// fp64 matrix cores, v_mfma_f64_16x16x4: 77.8 TFLOP/s in a loop of nothing else (with its
+// accumulators in VGPRs; copied to AGPRs and back they reach 47) against the vector
+// unit's 67.8, one instruction for every 16 FMA, and ten LDS reads for a wave's 16 products
+// of four records instead of nine reads for every 64 FMA of one.  Its accumulators are the
+// 8 x 8 blocks (the operand rows are permuted to make them so).
 //
 //   commit   : reconstruct S_p = Gamma_{1:p}[C dequant(Z) + K~ U~^T]
 //              + sum_j Gamma_{j+1:p} k~_j u_j^T  (Sec. 3.4 Eq. (smooth)),
@@ -154,7 +158,7 @@ struct TileShared {
             double part[2][NW][D];          // per-wave partials of a sum over key channels, two in turn
             double nrm[2][NW];              // per-wave partial squared norms
             int ex[2][NW];                  // per-wave largest exponent of a squared row norm
-            double vec[NW][D];              // a wave's copy of a summed vector (VP order)
+            double vec[NW][D];              // a wave's copy of a summed vector (order below)
             double red[TT / 16][8 * 17];    // row-private transposes of a sum over value channels
         };
     };
@@ -276,7 +280,7 @@ __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" :
 // count it has just made.
 template <int GATE, int CODE, int MODE>
 __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared<CODE> &sh, int tile, int p_given) {
-    // lane coordinates: value block i, row j of the wave, wave w; re-derived from
+    // lane coordinates: column i and row j in the wave, key block kb, wave w; re-derived from
     // an opaque thread index at phase boundaries, so that the compiler recomputes
     // the addresses built from them instead of holding them across phases
     int tid = threadIdx.x, i = tid & 15, j = (tid >> 4) & 3, kb = tid >> 4;
@@ -432,7 +436,10 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared<CODE> &s
             int lo, n;
             bounds(t, lo, n);
             const bool rec = t < nrp;
-            if (MODE == TILE_COMMIT && t == 0) wait_vm<NCP>();    // the first pass has landed (the codes may follow)
+            // the first pass has landed; a commit's codes may follow (with a scalar gate they
+            // too are waited for: the compiler waits for its load of the decays, and cannot
+            // count the copies issued after it)
+            if (MODE == TILE_COMMIT && t == 0) wait_vm<NCP>();
             else wait_vm_all();
             {
                 // keys: lane (c, h) folds the decay into slots 7 - 4 h - e, e = 0..3, newest first
@@ -629,9 +636,11 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, TileShared<CODE> &s
         // Sweeps without normalisation: each is scaled by one power of two (exact, so
         // only the direction matters), the first also by one near 1/|x|, and the
         // vector is normalised once after the last.  With 2^(e-1) <= n < 2^e for the
-        // largest squared row norm n, n <= sigma_1^2 <= |M|_F^2 <= 128 n: a sweep
-        // scaled by 2^-(e+3) changes the norm by a factor in about 2^-4 .. 2^4, far
-        // from the ends of the range for every sweep count.
+        // largest squared row norm n, n <= sigma_1^2 <= |M|_F^2 <= 128 n: a sweep scaled by
+        // 2^-(e+3) grows no vector by more than 2^4, and shrinks the part along the leading
+        // direction by no more than 2^-4, far from the ends of the range for every sweep
+        // count.  (A start vector without such a part may shrink to 0: rows v and -v have
+        // the start (1, 1) and M^T (1, 1) = 0.  The pair is then zero, as the method's.)
         double sc = 0.0;
 #pragma unroll 1
         for (int it = 0; it < A.power_iters; ++it) {
