@@ -148,3 +148,22 @@ def test_the_sweeps_stay_in_range_at_extreme_magnitudes(scale, sweeps):
         for f in ("Kt", "Ut"):
             with np.errstate(over="ignore"):
                 assert int((H.f16_bits(rep[f][i][:n]) != H.f16_bits(getattr(want, f)[:n])).sum()) == 0, (i, f)
+
+
+@pytest.mark.parametrize("code", [synth.CODE_INT8, synth.CODE_BF16])
+def test_a_corrupt_tile_among_others_leaves_them_alone(code):
+    """An export's copies into LDS start before rec_len is known: a tile that then turns out corrupt leaves its own
+    output as it was, and no copy of its behind in the LDS of the tiles that follow it on the CU."""
+    n = 4096
+    wl = synth.Workload("corrupt", n, 1, 1, 0, 4, 0, synth.GATE_SCALAR, code=code)
+    dims = H.gdims(wl)
+    st = B.State.empty(dims)
+    S = torch.randn((n, 128, 128), generator=torch.Generator(device="cuda").manual_seed(7), device="cuda")
+    B.leapquant_quantize_state(dims, S, st)
+    whole, some = torch.empty_like(S), torch.full_like(S, 9.0)
+    B.leapquant_dequantize_state(dims, st, whole)
+    bad = torch.arange(n, device="cuda") % 3 != 0
+    st.rec_len.view(-1)[bad] = torch.where(torch.arange(n, device="cuda") % 3 == 1, -1, 5).to(torch.int32)[bad]
+    B.leapquant_dequantize_state(dims, st, some)
+    assert B.leapquant_check_error(st) == B.LQ_DEVERR_BAD_REC_LEN
+    assert torch.equal(some[~bad], whole[~bad]) and bool((some[bad] == 9.0).all())
